@@ -13,12 +13,12 @@
 #include <mutex>
 #include <new>
 #include <string>
-#include <thread>
 #include <utility>
 #include <vector>
 
 #include "gmg.h"
 #include "gmg_fine.hpp"
+#include "gmg_coarse.hpp"
 #include "gmg_step.hpp"
 #include "gmg_krylov.hpp"
 #include "gmg_cheb.hpp"
@@ -30,9 +30,9 @@ namespace {
 
 constexpr size_t ALIGN = 256;
 constexpr int MAX_RESTART = 32;
-// coarsest levels of more cells than this are inverted on the GPU
-// (Gauss-Jordan), smaller ones on the host (Cholesky)
-constexpr int GJ_MIN_CELLS = 1024;
+// device scalars after the Krylov methods': the failed-pivot flag of the
+// coarsest level's inverse
+constexpr int MISC_BAD_PIVOT = 30;
 constexpr double BREAKDOWN_TOL = 1e-14;
 constexpr int CHEB_ARNOLDI = 10;  // Arnoldi steps of the Chebyshev bound estimate
 constexpr int CHEB_DEGREE = 2;    // degree of the Chebyshev smoothing polynomial
@@ -79,7 +79,7 @@ struct Layout {
   std::vector<LevelShape> shapes;
   std::vector<LevelOffsets> lv;
   size_t V, Z, a32, b0, xs, partials, scal, cinv, bargs, total;
-  size_t cgjm, cgjb;  // GPU inverse of a large coarsest level: float64 matrix (mixed), row / column buffers
+  size_t cmat;  // mixed: float64 matrix of the coarsest level while it is inverted (in float64, cinv itself)
   size_t cr0, cd0;  // Chebyshev smoother, finest level: float64 natural residual, T colour-split direction
   size_t rr;        // transpose restriction: residual of the level being restricted (finest: float64)
   size_t chs;       // Chebyshev smoother: device scalars of every level's bound estimate
@@ -183,8 +183,11 @@ int make_layout(int nx, int ny, int nz, double hx, double hy, double hz, const g
   L->scal = take((size_t)(L->m * (L->m + 2) + (L->m + 2) + 32) * 8);
   const size_t nc = last.n();
   L->cinv = take(nc * nc * L->tsize);
-  L->cgjm = nc > GJ_MIN_CELLS && mixed ? take(nc * nc * 8) : 0;
-  L->cgjb = nc > GJ_MIN_CELLS ? take(2 * nc * 8) : 0;
+  // the Krylov basis is free during a renewal and holds the matrix unless the
+  // grid has few levels
+  L->cmat = !mixed ? 0 : nc * nc * 8 <= (size_t)nvslots * L->ldv * 8 ? L->V : take(nc * nc * 8);
+  static_assert((size_t)NB * 4096 * 8 <= (size_t)MAXV * MAX_RED_BLOCKS * 8,
+                "the block column of the coarsest level's inverse does not fit the partials");
   L->bargs = take(sizeof(BottomArgs<double>));
   L->total = off;
   return GMG_OK;
@@ -354,147 +357,51 @@ void note(gmg_ctx* c, hipError_t e) {
   if (e != hipSuccess && c->err == hipSuccess) c->err = e;
 }
 
+int read_back(gmg_ctx* c, const double* dev, int n) {
+  note(c, hipMemcpyAsync(c->pinned, dev, (size_t)n * 8, hipMemcpyDeviceToHost, c->stream));
+  note(c, hipStreamSynchronize(c->stream));
+  return c->err == hipSuccess ? GMG_OK : GMG_ERR_HIP;
+}
+
 // ---------------------------------------------------------------------------
 // Hierarchy set-up (per coefficient).
 // ---------------------------------------------------------------------------
 
-// Cholesky factor and inverse of the symmetric positive definite n x n
-// matrix M (row-major), in place; returns false if not positive definite.
-// The inverse is formed column by column from L L^T x = e_c (the forward
-// solve starts at row c, where e_c's solution becomes nonzero), the columns
-// split over host threads; L^T is kept row-major for the backward solves.
-// sum_{k in [k0, k1)} x[k] y[k] in four interleaved partial sums (lets the
-// host compiler vectorise the loop without reassociating it itself)
-double dot4(const double* x, const double* y, int k0, int k1) {
-  double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-  int k = k0;
-  for (; k + 3 < k1; k += 4) {
-    s0 += x[k] * y[k];
-    s1 += x[k + 1] * y[k + 1];
-    s2 += x[k + 2] * y[k + 2];
-    s3 += x[k + 3] * y[k + 3];
-  }
-  for (; k < k1; ++k) s0 += x[k] * y[k];
-  return (s0 + s1) + (s2 + s3);
-}
-
-bool spd_inverse(std::vector<double>& M, int n) {
-  std::vector<double> Lf(M);
-  for (int j = 0; j < n; ++j) {
-    const double* lj = &Lf[(size_t)j * n];
-    double d = Lf[(size_t)j * n + j] - dot4(lj, lj, 0, j);
-    if (!(d > 0.0)) return false;
-    d = std::sqrt(d);
-    Lf[(size_t)j * n + j] = d;
-    for (int i = j + 1; i < n; ++i) {
-      const double* li = &Lf[(size_t)i * n];
-      Lf[(size_t)i * n + j] = (li[j] - dot4(li, lj, 0, j)) / d;
-    }
-  }
-  std::vector<double> Lt((size_t)n * n, 0.0);  // Lt[i][k] = L[k][i]
-  for (int i = 0; i < n; ++i)
-    for (int k = 0; k <= i; ++k) Lt[(size_t)k * n + i] = Lf[(size_t)i * n + k];
-  auto columns = [&](int c0, int c1) {
-    std::vector<double> col(n);
-    for (int c = c0; c < c1; ++c) {
-      std::fill(col.begin(), col.begin() + c, 0.0);
-      for (int i = c; i < n; ++i) {
-        const double* li = &Lf[(size_t)i * n];
-        col[i] = ((i == c ? 1.0 : 0.0) - dot4(li, col.data(), c, i)) / li[i];
-      }
-      for (int i = n - 1; i >= 0; --i) {
-        const double* ti = &Lt[(size_t)i * n];
-        col[i] = (col[i] - dot4(ti, col.data(), i + 1, n)) / ti[i];
-      }
-      for (int i = 0; i < n; ++i) M[(size_t)i * n + c] = col[i];
-    }
-  };
-  const int nt = std::max(1, std::min<int>(16, (int)std::thread::hardware_concurrency()));
-  if (n < 256 || nt == 1) {
-    columns(0, n);
-  } else {
-    std::vector<std::thread> pool;
-    for (int t = 0; t < nt; ++t) pool.emplace_back(columns, (int)((long long)n * t / nt), (int)((long long)n * (t + 1) / nt));
-    for (auto& th : pool) th.join();
-  }
-  // symmetrise the rounding
-  for (int i = 0; i < n; ++i)
-    for (int j = i + 1; j < n; ++j) {
-      const double v = 0.5 * (M[(size_t)i * n + j] + M[(size_t)j * n + i]);
-      M[(size_t)i * n + j] = M[(size_t)j * n + i] = v;
-    }
-  return true;
-}
-
-// Dense matrix of the coarsest level from its face coefficients (host).
-void assemble_coarsest(const LevelShape& s, const std::vector<double>& wx, const std::vector<double>& wy,
-                       const std::vector<double>& wz, const std::vector<double>& tp, const double* a_fine,
-                       bool fine_cells, std::vector<double>& M) {
-  const int nx = s.nx, ny = s.ny, nz = s.nz;
-  const int n = nx * ny * nz;
-  const double ix = 1.0 / (s.hx * s.hx), iy = 1.0 / (s.hy * s.hy), iz = 1.0 / (s.hz * s.hz);
-  M.assign((size_t)n * n, 0.0);
-  auto id = [&](int i, int j, int k) { return (k * ny + j) * nx + i; };
-  auto couple = [&](int p, int q, double w) {
-    M[(size_t)p * n + p] += w;
-    M[(size_t)q * n + q] += w;
-    M[(size_t)p * n + q] -= w;
-    M[(size_t)q * n + p] -= w;
-  };
-  for (int k = 0; k < nz; ++k)
-    for (int j = 0; j < ny; ++j)
-      for (int i = 0; i < nx; ++i) {
-        const int c = id(i, j, k);
-        if (fine_cells) {  // single-level grid: faces from the cell coefficient
-          const double ac = a_fine[c];
-          if (i + 1 < nx) couple(c, id(i + 1, j, k), 0.5 * (ac + a_fine[id(i + 1, j, k)]) * ix);
-          if (j + 1 < ny) couple(c, id(i, j + 1, k), 0.5 * (ac + a_fine[id(i, j + 1, k)]) * iy);
-          if (k + 1 < nz) couple(c, id(i, j, k + 1), 0.5 * (ac + a_fine[id(i, j, k + 1)]) * iz);
-          if (k == 0) M[(size_t)c * n + c] += 2.0 * ac * iz;
-          if (k == nz - 1) M[(size_t)c * n + c] += 2.0 * ac * iz;
-        } else {
-          if (i + 1 < nx) couple(c, id(i + 1, j, k), wx[id(i + 1, j, k)] * ix);
-          if (j + 1 < ny) couple(c, id(i, j + 1, k), wy[id(i, j + 1, k)] * iy);
-          if (k + 1 < nz) couple(c, id(i, j, k + 1), wz[id(i, j, k + 1)] * iz);
-          if (k == 0) M[(size_t)c * n + c] += 2.0 * wz[c] * iz;
-          if (k == nz - 1) M[(size_t)c * n + c] += 2.0 * tp[j * nx + i] * iz;
-        }
-      }
-}
-
-// Inverse of the coarsest matrix M (n x n, SPD, row-major host copy) on the
-// GPU by in-place Gauss-Jordan elimination without pivoting (every pivot of
-// an SPD matrix is positive): n steps, each saving row and column k, then
-// updating every element.  O(n^3) work spread over the GPU instead of the
-// host's O(n^3) Cholesky inverse (about 20 s at n = 4096 on 8 host cores);
-// the result lands in cinv in the V-cycle precision.
-int gpu_inverse(gmg_ctx* c, const std::vector<double>& M, int n) {
+// Inverse of the coarsest level's matrix into cinv (V-cycle precision), on the
+// GPU at every size (gmg_coarse.hpp): assembly, the symmetric sweep in NB x NB
+// blocks on the float64 matrix, and the copy of both triangles.  Nothing of
+// it visits the host but the failed-pivot flag.
+int coarse_inverse(gmg_ctx* c) {
   const Layout& L = c->L;
-  double* A = c->mixed ? wsp<double>(c, L.cgjm) : wsp<double>(c, L.cinv);
-  double* rk = wsp<double>(c, L.cgjb);
-  double* ck = rk + n;
-  note(c, hipMemcpyAsync(A, M.data(), (size_t)n * n * 8, hipMemcpyHostToDevice, c->stream));
-  const Launch vl{dim3((unsigned)((n + 255) / 256)), dim3(256, 1, 1), 0};
-  const Launch ml{dim3((unsigned)((n + 255) / 256), (unsigned)n), dim3(256, 1, 1), 0};
-  for (int k = 0; k < n; ++k) {
-    GMG_LAUNCH(c, "gj_save", k_gj_save, vl, (const double*)A, n, k, rk, ck);
-    GMG_LAUNCH(c, "gj_step", k_gj_step, ml, A, n, k, (const double*)rk, (const double*)ck);
+  const int nl = (int)L.shapes.size();
+  const LevelShape& s = L.shapes.back();
+  const int n = (int)s.n(), nb = (n + NB - 1) / NB;
+  double* A = c->mixed ? wsp<double>(c, L.cmat) : wsp<double>(c, L.cinv);
+  double* C = wsp<double>(c, L.partials);  // n x NB
+  double* bad = scal_misc(c) + MISC_BAD_PIVOT;
+  FaceCoef<double> co{};
+  if (nl > 1) {
+    const LevelOffsets& o = L.lv[nl - 1];
+    co = FaceCoef<double>{wsp<double>(c, o.wx64), wsp<double>(c, o.wy64), wsp<double>(c, o.wz64),
+                          wsp<double>(c, o.tp64)};
   }
-  // the diagonal of an SPD inverse is positive
-  GMG_LAUNCH(c, "gj_diag", k_gj_diag, vl, (const double*)A, n, rk);
-  std::vector<double> d(n);
-  note(c, hipMemcpyAsync(d.data(), rk, (size_t)n * 8, hipMemcpyDeviceToHost, c->stream));
-  note(c, hipStreamSynchronize(c->stream));
-  if (c->err != hipSuccess) return GMG_ERR_HIP;
-  for (double v : d)
-    if (!(v > 0.0) || !std::isfinite(v)) return GMG_ERR_NONFINITE;
-  if (c->mixed) {
-    const size_t nn = (size_t)n * n;
-    GMG_LAUNCH(c, "convert_f64_f32", (k_convert<float, double>), flat_launch(nn), (const double*)A,
-               wsp<float>(c, L.cinv), nn);
-    note(c, hipStreamSynchronize(c->stream));
+  const dim3 block(INV_THREADS, 1, 1);
+  GMG_LAUNCH(c, "coarse_assemble", k_dense_assemble,
+             (Launch{dim3((unsigned)((n + 255) / 256), (unsigned)n), dim3(256, 1, 1), 0}), co,
+             nl == 1 ? c->a : (const double*)nullptr, s.geom(), n, A);
+  GMG_LAUNCH(c, "coarse_inverse", k_sweep_first, (Launch{dim3(1), block, 0}), A, n, bad);
+  for (int k = 0; k < nb && nb > 1; ++k) {
+    GMG_LAUNCH(c, "coarse_inverse", k_sweep_panel, (Launch{dim3((unsigned)nb), block, 0}), A, n, k, C);
+    GMG_LAUNCH(c, "coarse_inverse", k_sweep_update, (Launch{dim3((unsigned)(1 + nb * (nb + 1) / 2)), block, 0}), A, n,
+               nb, k, (const double*)C, bad);
   }
-  return c->err == hipSuccess ? GMG_OK : GMG_ERR_HIP;
+  const Launch fl{dim3((unsigned)nb, (unsigned)nb), block, 0};
+  if (c->mixed)
+    GMG_LAUNCH(c, "coarse_inverse", k_sweep_finish<float>, fl, (const double*)A, n, wsp<float>(c, L.cinv));
+  else
+    GMG_LAUNCH(c, "coarse_inverse", k_sweep_finish<double>, fl, (const double*)A, n, wsp<double>(c, L.cinv));
+  if (read_back(c, bad, 1) != GMG_OK) return GMG_ERR_HIP;
+  return c->pinned[0] == 0.0 ? GMG_OK : GMG_ERR_NONFINITE;
 }
 
 int build_hierarchy(gmg_ctx* c) {
@@ -551,39 +458,7 @@ int build_hierarchy(gmg_ctx* c) {
                  wsp<float>(c, o.tp), nxy);
     }
   }
-  // coarsest level: dense matrix on the host, Cholesky inverse, upload
-  const LevelShape& s = L.shapes.back();
-  const int n = (int)s.n();
-  std::vector<double> wx, wy, wz, tp, afine, M;
-  if (nl == 1) {
-    afine.resize(n);
-    note(c, hipMemcpyAsync(afine.data(), c->a, (size_t)n * 8, hipMemcpyDeviceToHost, c->stream));
-  } else {
-    const LevelOffsets& o = L.lv[nl - 1];
-    const size_t nxy = (size_t)s.nx * s.ny;
-    wx.resize(n);
-    wy.resize(n);
-    wz.resize(n);
-    tp.resize(nxy);
-    note(c, hipMemcpyAsync(wx.data(), wsp<double>(c, o.wx64), (size_t)n * 8, hipMemcpyDeviceToHost, c->stream));
-    note(c, hipMemcpyAsync(wy.data(), wsp<double>(c, o.wy64), (size_t)n * 8, hipMemcpyDeviceToHost, c->stream));
-    note(c, hipMemcpyAsync(wz.data(), wsp<double>(c, o.wz64), (size_t)n * 8, hipMemcpyDeviceToHost, c->stream));
-    note(c, hipMemcpyAsync(tp.data(), wsp<double>(c, o.tp64), nxy * 8, hipMemcpyDeviceToHost, c->stream));
-  }
-  note(c, hipStreamSynchronize(c->stream));
-  if (c->err != hipSuccess) return GMG_ERR_HIP;
-  assemble_coarsest(s, wx, wy, wz, tp, afine.data(), nl == 1, M);
-  if (n > GJ_MIN_CELLS) return gpu_inverse(c, M, n);
-  if (!spd_inverse(M, n)) return GMG_ERR_NONFINITE;
-  if (c->mixed) {
-    std::vector<float> Mf(M.begin(), M.end());
-    note(c, hipMemcpyAsync(wsp<float>(c, L.cinv), Mf.data(), Mf.size() * 4, hipMemcpyHostToDevice, c->stream));
-    note(c, hipStreamSynchronize(c->stream));
-  } else {
-    note(c, hipMemcpyAsync(wsp<double>(c, L.cinv), M.data(), M.size() * 8, hipMemcpyHostToDevice, c->stream));
-    note(c, hipStreamSynchronize(c->stream));
-  }
-  return c->err == hipSuccess ? GMG_OK : GMG_ERR_HIP;
+  return coarse_inverse(c);
 }
 
 // ---------------------------------------------------------------------------
@@ -841,7 +716,7 @@ void restrict_mean(gmg_ctx* c, int l) {
 template <typename T>
 void coarse_solve(gmg_ctx* c, const T* b, T* x) {
   const int n = c->nc;
-  const Launch lc{dim3((n + NTHREADS - 1) / NTHREADS), dim3(BX, BY, 1), 0};
+  const Launch lc{dim3((n + BY - 1) / BY), dim3(BX, BY, 1), 0};
   GMG_LAUNCH(c, kname("coarse_solve", -1, sizeof(T)), k_coarse_solve<T>, lc,
              wsp<const T>(c, c->L.cinv), b, x, n);
 }
@@ -1581,12 +1456,6 @@ void update_solution(gmg_ctx* c, double* phi, int k, bool set) {
     else
       update_nv<double>(nq, c, fl, phi, (const double*)Zb, y, st, seq);
   }
-}
-
-int read_back(gmg_ctx* c, const double* dev, int n) {
-  note(c, hipMemcpyAsync(c->pinned, dev, (size_t)n * 8, hipMemcpyDeviceToHost, c->stream));
-  note(c, hipStreamSynchronize(c->stream));
-  return c->err == hipSuccess ? GMG_OK : GMG_ERR_HIP;
 }
 
 bool valid_ctx(gmg_ctx* c) { return c != nullptr; }
