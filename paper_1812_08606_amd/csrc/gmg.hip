@@ -2403,6 +2403,14 @@ int gmg_krylov_solve(gmg_ctx* c, int method, const double* f_dev, double phi_bot
 
 int gmg_apply_operator(gmg_ctx* c, const double* x_dev, double* y_dev, double phi_bot, double phi_top) {
   if (!valid_ctx(c) || !x_dev || !y_dev) return GMG_ERR_ARG;
+  auto a16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
+  if (c->nx % 2 == 0 && a16(x_dev) && a16(c->a) && a16(y_dev)) {  // pairs are 16-byte loads and stores
+    // (z-chunks from 4 to 64 planes were within 6% of each other from 128^3 to 512^3)
+    const Launch lp = pair_launch(c->nx, c->ny, c->nz, 4096, 8, 2);
+    GMG_LAUNCH(c, "apply_bc", k_apply_bc_pair, lp, x_dev, c->a, c->L.shapes[0].geom(), phi_bot, phi_top, y_dev, lp.kc);
+    note(c, hipStreamSynchronize(c->stream));
+    return c->err == hipSuccess ? GMG_OK : GMG_ERR_HIP;
+  }
   const Launch lc = col_launch(c->nx, c->ny, c->nz, 1 << 16);
   GMG_LAUNCH(c, "apply_bc", k_apply_bc, lc, x_dev, c->a, c->L.shapes[0].geom(), phi_bot, phi_top, y_dev, lc.kc);
   note(c, hipStreamSynchronize(c->stream));
