@@ -18,6 +18,7 @@
 
 #include "gmg.h"
 #include "gmg_fine.hpp"
+#include "gmg_bottom.hpp"
 #include "gmg_coarse.hpp"
 #include "gmg_step.hpp"
 #include "gmg_krylov.hpp"
@@ -78,7 +79,7 @@ struct LevelOffsets {
 struct Layout {
   std::vector<LevelShape> shapes;
   std::vector<LevelOffsets> lv;
-  size_t V, Z, a32, b0, xs, partials, scal, cinv, bargs, total;
+  size_t V, Z, a32, b0, xs, partials, scal, cinv, total;
   size_t cmat;  // mixed: float64 matrix of the coarsest level while it is inverted (in float64, cinv itself)
   size_t cr0, cd0;  // Chebyshev smoother, finest level: float64 natural residual, T colour-split direction
   size_t rr;        // transpose restriction: residual of the level being restricted (finest: float64)
@@ -188,7 +189,6 @@ int make_layout(int nx, int ny, int nz, double hx, double hy, double hz, const g
   L->cmat = !mixed ? 0 : nc * nc * 8 <= (size_t)nvslots * L->ldv * 8 ? L->V : take(nc * nc * 8);
   static_assert((size_t)NB * 4096 * 8 <= (size_t)MAXV * MAX_RED_BLOCKS * 8,
                 "the block column of the coarsest level's inverse does not fit the partials");
-  L->bargs = take(sizeof(BottomArgs<double>));
   L->total = off;
   return GMG_OK;
 }
@@ -199,6 +199,7 @@ int make_layout(int nx, int ny, int nz, double hx, double hy, double hz, const g
 // remain; -1 when that leaves only the coarsest (a plain direct solve).
 constexpr size_t BOTTOM_MAX_CELLS = 4096;
 constexpr size_t BOTTOM_MAX_COARSEST = 512;
+constexpr size_t BOTTOM_MAX_SUM = 4704;  // >= 4096 (1 + 1/8 + 1/64 + ...)
 
 int bottom_level(const Layout& L) {
   const int nl = (int)L.shapes.size();
@@ -206,7 +207,7 @@ int bottom_level(const Layout& L) {
   int l = nl - 1;
   size_t cells = L.shapes[l].n();
   while (l > 1 && L.shapes[l - 1].n() <= BOTTOM_MAX_CELLS && nl - (l - 1) <= BOTTOM_MAX_LEVELS &&
-         cells + L.shapes[l - 1].n() <= (size_t)BOTTOM_LDS_CELLS) {
+         cells + L.shapes[l - 1].n() <= BOTTOM_MAX_SUM) {
     --l;
     cells += L.shapes[l].n();
   }
@@ -721,47 +722,41 @@ void coarse_solve(gmg_ctx* c, const T* b, T* x) {
              wsp<const T>(c, c->L.cinv), b, x, n);
 }
 
-// The levels from l0 down to the coarsest in one workgroup (k_vcycle_bottom):
-// a V-cycle, or the full multigrid cycle over those levels when fmg; its
-// arguments were written to the workspace at set-up.
+// Arguments of the bottom kernel.
 template <typename T>
-void vcycle_bottom(gmg_ctx* c, int fmg) {
-  const Launch one{dim3(1), dim3(BottomThreads<T>::value, 1, 1), 0};
-  if (fmg)
-    GMG_LAUNCH(c, kname("fmg_bottom", c->bottom_from, sizeof(T)), (k_vcycle_bottom<T, true>), one,
-               wsp<const BottomArgs<T>>(c, c->L.bargs));
-  else
-    GMG_LAUNCH(c, kname("vcycle_bottom", c->bottom_from, sizeof(T)), (k_vcycle_bottom<T, false>), one,
-               wsp<const BottomArgs<T>>(c, c->L.bargs));
-}
-
-// Arguments of the bottom kernel (fixed for the life of the context).
-template <typename T>
-int write_bottom_args(gmg_ctx* c) {
+BottomArgs<T> bottom_args(gmg_ctx* c) {
   const int nl = (int)c->L.shapes.size(), l0 = c->bottom_from;
-  if (l0 < 0) return GMG_OK;
   BottomArgs<T> A{};
   A.nlev = nl - l0;
-  int coff = 0, tpoff = 0;
+  int off = 0;
   for (int q = 0; q < A.nlev; ++q) {
-    const int l = l0 + q;
-    const LevelShape& s = c->L.shapes[l];
-    A.co[q] = face_coef<T>(c, l);
+    const LevelShape& s = c->L.shapes[l0 + q];
+    A.co[q] = face_coef<T>(c, l0 + q);
     A.g[q] = s.geom();
-    A.coff[q] = coff;
-    A.tpoff[q] = tpoff;
-    coff += (int)s.n();
-    tpoff += s.nx * s.ny;
+    if (q == A.nlev - 1) break;
+    const int plane = s.nx / 2 * s.ny;
+    A.xoff[q] = off + plane;  // a plane of zeros below and above
+    off += (s.nz + 2) * plane;
   }
-  if (coff > BOTTOM_LDS_CELLS || tpoff > BOTTOM_LDS_CELLS) return GMG_ERR_SHAPE;
   A.x0 = wsp<T>(c, c->L.lv[l0].x);
   A.b0 = wsp<T>(c, c->L.lv[l0].b);
   A.Ainv = wsp<const T>(c, c->L.cinv);
   A.nu_pre = c->opt.nu_pre;
   A.nu_post = c->opt.nu_post;
-  note(c, hipMemcpyAsync(wsp<BottomArgs<T>>(c, c->L.bargs), &A, sizeof(A), hipMemcpyHostToDevice, c->stream));
-  note(c, hipStreamSynchronize(c->stream));
-  return c->err == hipSuccess ? GMG_OK : GMG_ERR_HIP;
+  return A;
+}
+
+// The levels from bottom_from down to the coarsest in one workgroup
+// (k_vcycle_bottom): a V-cycle, or the full multigrid cycle over those
+// levels when fmg.
+template <typename T>
+void vcycle_bottom(gmg_ctx* c, int fmg) {
+  const Launch one{dim3(1), dim3(BottomShape<T>::threads, 1, 1), 0};
+  const BottomArgs<T> A = bottom_args<T>(c);
+  if (fmg)
+    GMG_LAUNCH(c, kname("fmg_bottom", c->bottom_from, sizeof(T)), (k_vcycle_bottom<T, true>), one, A);
+  else
+    GMG_LAUNCH(c, kname("vcycle_bottom", c->bottom_from, sizeof(T)), (k_vcycle_bottom<T, false>), one, A);
 }
 
 // Chebyshev smoothing (Sec. 3.2, eq. qntn) on a coarse level l: nu
@@ -2069,8 +2064,7 @@ int init_ctx(gmg_ctx* c, int nx, int ny, int nz, double hx, double hy, double hz
   c->sn.assign(m, 0.0);
   c->g.assign(m + 1, 0.0);
   c->y.assign(m, 0.0);
-  int r = c->mixed ? write_bottom_args<float>(c) : write_bottom_args<double>(c);
-  if (r == GMG_OK) r = build_hierarchy(c);
+  int r = build_hierarchy(c);
   if (r == GMG_OK && opt->smoother == GMG_SMOOTH_CHEBYSHEV)
     r = c->mixed ? cheb_estimate<float>(c) : cheb_estimate<double>(c);
   return r;
