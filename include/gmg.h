@@ -123,7 +123,11 @@ typedef struct gmg_options {
                            elsewhere);
                            GMG_SWEEP_AUTO (default): fused where it was
                            measured faster (finest level: long z-chunks;
-                           coarse levels: at least 128^3 cells) */
+                           coarse levels: at least 128^3 cells), and on levels
+                           whose iterate has at most 4 MiB several sweeps per
+                           kernel, with the interpolation or the residual
+                           restriction in it (nu_pre, nu_post >= 1, mean
+                           restriction) */
   int cold_cycle;       /* preconditioner of a solve with use_x0 = 0: GMG_CYCLE_FMG
                            (default) one full multigrid cycle per step,
                            GMG_CYCLE_V one V-cycle per step. */

@@ -20,6 +20,7 @@
 #include "gmg_fine.hpp"
 #include "gmg_bottom.hpp"
 #include "gmg_coarse.hpp"
+#include "gmg_leg.hpp"
 #include "gmg_step.hpp"
 #include "gmg_krylov.hpp"
 #include "gmg_cheb.hpp"
@@ -286,6 +287,13 @@ struct gmg_ctx {
   int nc;  // cells on the coarsest level
   int cus;  // compute units of the device
   int bottom_from;  // first level run by the one-workgroup bottom kernel (-1: none)
+  // levels whose visits run as legs (k_leg): launches of the pre- and
+  // post-smoothing, empty where the level runs per-sweep kernels
+  struct LegPlan {
+    int sweeps;  // symmetric sweeps of the launch
+    int tx, ty, tz, hx, hy;
+  };
+  std::vector<std::array<std::vector<LegPlan>, 3>> legs;  // per level: pre from zero, pre from a guess, post
   bool fmg_now;     // the running solve preconditions with full multigrid cycles
   bool gmres_mode;  // GMRES: one preconditioned-vector slot, x updated by M (V y)
   int nprec;        // preconditioner applications of the running solve
@@ -798,6 +806,137 @@ void cheb_smooth_face(gmg_ctx* c, int l, T* x, const T* b, const FaceCoef<T>& co
   }
 }
 
+// ---------------------------------------------------------------------------
+// Legs of small levels (k_leg).
+// ---------------------------------------------------------------------------
+
+// Levels whose iterate has at most this many bytes run as legs: about 10^6
+// cells in float32, half of that in float64.  Measured, one full multigrid
+// cycle and Arnoldi step with per-sweep kernels and with legs on that level:
+// float32 64^3 182 -> 170 us, 80^3 228 -> 217, 96^3 246 -> 247 (V-cycle 145 ->
+// 139), 112^3 403 -> 428; float64 64^3 205 -> 199, 80^3 300 -> 297, 96^3 298 ->
+// 323.  (All levels below included: 64^3 222 -> 170 us, 32^3 123 -> 104.)
+constexpr size_t LEG_MAX_BYTES = (size_t)4 << 20;
+
+// Time of one launch of a leg (clocks, a model fitted to the bottom kernel's
+// and the leg's measured phases): launch and first loads, then per pair of
+// the box with its halo the loads and each half-sweep, times the rounds of
+// blocks (one per CU).
+template <typename T>
+double leg_cost(long long blocks, int pairs, int nh, int cus) {
+  const double load = sizeof(T) == 4 ? 1.6 : 3.2, half = sizeof(T) == 4 ? 0.55 : 0.75;
+  return 9000.0 + (double)((blocks + cus - 1) / cus) * (4000.0 + pairs * (load + half * nh));
+}
+
+// The cheapest box for `sweeps` symmetric sweeps on level s: halo of 2 sweeps
+// cells (one more with the residual, one less from x = 0).
+template <typename T>
+bool leg_box(const LevelShape& s, int sweeps, bool zero, bool resid, int cus, gmg_ctx::LegPlan& best, double& cost) {
+  const int nh = 2 * sweeps, R = nh + (resid ? 1 : 0) - (zero ? 1 : 0), H = s.nx / 2;
+  cost = 1e300;
+  for (int tx = H;; tx = (tx + 1) / 2) {
+    const int hx = tx == H ? 0 : (R + 1) / 2;
+    for (int ty = 2; ty <= 16; ty += 2)
+      for (int tz = 2; tz <= 16; tz += 2) {
+        const int rx = tx + 2 * hx, ry = ty + 2 * R, rz = tz + 2 * R, pairs = rx * ry * rz;
+        if (pairs > LegShape<T>::max_pairs || rx * (ry + 2) * (rz + 2) + 2 > LegShape<T>::lds ||
+            tx * ty * tz > LegShape<T>::own)
+          continue;
+        const long long blocks = (long long)((H + tx - 1) / tx) * ((s.ny + ty - 1) / ty) * ((s.nz + tz - 1) / tz);
+        const double c = leg_cost<T>(blocks, pairs, nh, cus);
+        if (c < cost) {
+          cost = c;
+          best = {sweeps, tx, ty, tz, hx, R};
+        }
+      }
+    if (tx <= 8) break;
+  }
+  return cost < 1e300;
+}
+
+// Launches of one leg of nu sweeps: the split into launches that costs least.
+template <typename T>
+double leg_split(const LevelShape& s, int nu, bool zero, bool resid, int cus, std::vector<gmg_ctx::LegPlan>& out) {
+  double best = 1e300;
+  for (int first = 1; first <= std::min(nu, 3); ++first) {
+    gmg_ctx::LegPlan p{};
+    double c;
+    if (!leg_box<T>(s, first, zero, resid && first == nu, cus, p, c)) continue;
+    std::vector<gmg_ctx::LegPlan> rest;
+    if (first < nu) c += leg_split<T>(s, nu - first, false, resid, cus, rest);
+    if (c < best) {
+      best = c;
+      out.assign(1, p);
+      out.insert(out.end(), rest.begin(), rest.end());
+    }
+  }
+  return best;
+}
+
+template <typename T>
+void plan_legs(gmg_ctx* c) {
+  const int nl = (int)c->L.shapes.size(), npre = c->opt.nu_pre, npost = c->opt.nu_post;
+  c->legs.assign(nl, {});
+  if (c->opt.fine_sweep != GMG_SWEEP_AUTO || c->opt.smoother != GMG_SMOOTH_RBGS ||
+      c->opt.restriction != GMG_RESTRICT_MEAN || npre < 1 || npost < 1)
+    return;
+  for (int l = 0; l < nl - 1 && l != c->bottom_from; ++l) {
+    const LevelShape& s = c->L.shapes[l];
+    if (s.n() * sizeof(T) > LEG_MAX_BYTES) continue;
+    auto& p = c->legs[l];
+    const double a = leg_split<T>(s, npre, true, true, c->cus, p[0]);
+    const double b = leg_split<T>(s, npre, false, true, c->cus, p[1]);
+    const double d = leg_split<T>(s, npost, false, false, c->cus, p[2]);
+    if (a >= 1e300 || b >= 1e300 || d >= 1e300) p = {};
+  }
+}
+
+bool has_legs(gmg_ctx* c, int l) { return !c->legs[l][2].empty(); }
+
+template <typename T, bool FINE>
+void launch_leg(gmg_ctx* c, int l, const gmg_ctx::LegPlan& p, LegArgs<T>& A, const char* name) {
+  const LevelShape& s = c->L.shapes[l];
+  A.g = s.geom();
+  A.nh = 2 * p.sweeps;
+  A.tx = p.tx;
+  A.ty = p.ty;
+  A.tz = p.tz;
+  A.hx = p.hx;
+  A.hy = p.hy;
+  constexpr int NT = LegShape<T>::threads;
+  const Launch ln{dim3((s.nx / 2 + p.tx - 1) / p.tx, (s.ny + p.ty - 1) / p.ty, (s.nz + p.tz - 1) / p.tz),
+                  dim3(NT, 1, 1), 0};
+  const int pairs = (p.tx + 2 * p.hx) * (p.ty + 2 * p.hy) * (p.tz + 2 * p.hy);
+  constexpr int SMALL = sizeof(T) == 4 ? 2 : 3, LARGE = LegShape<T>::max_pairs / NT;
+  const char* nm = kname(name, l, sizeof(T));
+  if (pairs <= SMALL * NT)
+    GMG_LAUNCH(c, nm, (k_leg<T, SMALL, FINE>), ln, A);
+  else
+    GMG_LAUNCH(c, nm, (k_leg<T, LARGE, FINE>), ln, A);
+}
+
+// The launches of one leg of level l (`which`: 0 pre-smoothing from zero, 1
+// from the interpolated guess, 2 post-smoothing after the coarse
+// correction).  The launches of a visit (pre, then post) alternate between
+// the level's two iterates X[0], X[1] so that the last one lands in X[0];
+// `done` launches of `total` precede this leg.
+template <typename T, bool FINE>
+void run_leg(gmg_ctx* c, int l, int which, LegArgs<T> A, T* const (&X)[2], int done, int total) {
+  const auto& plan = c->legs[l][which];
+  T* const bc = which == 2 ? nullptr : wsp<T>(c, c->L.lv[l + 1].b);
+  A.c1 = which == 2 ? 1 : 0;
+  A.xc = wsp<const T>(c, c->L.lv[l + 1].x);
+  for (size_t i = 0; i < plan.size(); ++i) {
+    const int n = done + (int)i;
+    A.start = i > 0 ? LEG_X : which == 0 ? LEG_ZERO : which == 1 ? LEG_SET : LEG_ADD;
+    A.xin = X[(total - n) & 1];
+    A.xout = X[(total - 1 - n) & 1];
+    A.bc = i + 1 == plan.size() ? bc : nullptr;
+    launch_leg<T, FINE>(c, l, plan[i], A, which == 2 ? "leg_post" : "leg_pre");
+    A.u = nullptr;  // the first launch from zero has stored B
+  }
+}
+
 // Levels >= 1 (face coefficients), right side in lv[l].b, result in lv[l].x:
 // a V-cycle from x = 0, or from the guess in lv[l].x when from_x (the
 // coarsest level is solved directly either way; a guess is never passed to
@@ -817,6 +956,17 @@ void vcycle_coarse(gmg_ctx* c, int l, bool from_x = false) {
     return;
   }
   const FaceCoef<T> co = face_coef<T>(c, l);
+  if (has_legs(c, l)) {  // (a guess is P x of level l + 1, interpolated by the first launch)
+    LegArgs<T> A{};
+    A.co = co;
+    A.b = b;
+    T* const X[2] = {x, wsp<T>(c, o.x2)};
+    const int pre = from_x ? 1 : 0, npre = (int)c->legs[l][pre].size(), total = npre + (int)c->legs[l][2].size();
+    run_leg<T, false>(c, l, pre, A, X, 0, total);
+    vcycle_coarse<T>(c, l + 1);
+    run_leg<T, false>(c, l, 2, A, X, npre, total);
+    return;
+  }
   if (fused_face<T>(c, l)) {
     // the sweeps ping-pong between x and x2; the first buffer (from zero)
     // or an out-of-place prolongation (from the guess in x) makes the last
@@ -872,7 +1022,7 @@ void fmg_coarse(gmg_ctx* c, int l0) {
   else
     coarse_solve<T>(c, wsp<const T>(c, c->L.lv[nl - 1].b), wsp<T>(c, c->L.lv[nl - 1].x));
   for (int l = lb - 1; l >= l0; --l) {
-    prolong_set<T>(c, l, wsp<T>(c, c->L.lv[l].x), wsp<const T>(c, c->L.lv[l + 1].x));
+    if (!has_legs(c, l)) prolong_set<T>(c, l, wsp<T>(c, c->L.lv[l].x), wsp<const T>(c, c->L.lv[l + 1].x));
     vcycle_coarse<T>(c, l, true);
   }
 }
@@ -931,6 +1081,26 @@ void vcycle_fine_split(gmg_ctx* c, const double* u, const double* bscale, T* X, 
     gs_split<T, false>(c, X, B, nullptr, nullptr, a, 1);
     gs_split<T, false>(c, X, B, nullptr, nullptr, a, 0);
   }
+}
+
+// z = M (s * u) with the finest level's visit as legs; from_x: B already
+// holds the right side, the guess is P x of level 1.
+template <typename T>
+void vcycle_fine_legs(gmg_ctx* c, const double* u, const double* bscale, T* Z, bool from_x) {
+  LegArgs<T> A{};
+  A.a = c->mixed ? (const T*)wsp<float>(c, c->L.a32) : (const T*)c->a;
+  A.hn = c->L.hn;
+  A.b = A.bout = wsp<T>(c, c->L.b0);
+  T* const X[2] = {Z, wsp<T>(c, c->L.xs)};
+  const int pre = from_x ? 1 : 0, npre = (int)c->legs[0][pre].size(), total = npre + (int)c->legs[0][2].size();
+  if (!from_x) {
+    A.u = u;
+    A.bscale = bscale;
+  }
+  run_leg<T, true>(c, 0, pre, A, X, 0, total);
+  vcycle_coarse<T>(c, 1);
+  A.u = nullptr;
+  run_leg<T, true>(c, 0, 2, A, X, npre, total);
 }
 
 // z = M (s * u) with the Chebyshev smoother on the finest level (at least
@@ -1163,6 +1333,8 @@ void vcycle_fine(gmg_ctx* c, const double* u, const double* bscale, T* z) {
   }
   if (c->opt.smoother == GMG_SMOOTH_CHEBYSHEV)
     vcycle_fine_cheb<T>(c, u, bscale, z);
+  else if (has_legs(c, 0))
+    vcycle_fine_legs<T>(c, u, bscale, z, false);
   else if (fused_sweeps<T>(c))
     vcycle_fine_sym<T>(c, u, bscale, z, false);
   else
@@ -1188,6 +1360,10 @@ void fmg_fine(gmg_ctx* c, const double* u, const double* bscale, T* z) {
                wsp<T>(c, c->L.lv[1].b), s.geom(), hn);
   }
   fmg_coarse<T>(c, 1);
+  if (has_legs(c, 0)) {
+    vcycle_fine_legs<T>(c, u, bscale, z, true);
+    return;
+  }
   const bool fused = fused_sweeps<T>(c);
   T* X0 = fused ? sym_buffer<T>(c, z, 0) : z;
   {
@@ -2058,6 +2234,10 @@ int init_ctx(gmg_ctx* c, int nx, int ny, int nz, double hx, double hy, double hz
                  ? n
                  : 256;
   }
+  if (c->mixed)
+    plan_legs<float>(c);
+  else
+    plan_legs<double>(c);
   const int m = opt->restart;
   c->R.assign((size_t)m * m, 0.0);
   c->cs.assign(m, 0.0);

@@ -108,10 +108,11 @@ struct BottomPair {
   T b[2];                 // right side
 };
 
+// Weights and diagonals of the pair (m, j, k) of a level with stored faces.
 template <typename T>
-__device__ __forceinline__ void bottom_setup(BottomPair<T>& q, const FaceCoef<T>& co, const Geom& g, int xoff, int p) {
-  const BottomAt at(p, g.nx >> 1, g.ny);
-  const int H = g.nx >> 1, m = at.m, j = at.j, k = at.k;
+__device__ __forceinline__ void pair_weights(BottomPair<T>& q, const FaceCoef<T>& co, const Geom& g, int m, int j,
+                                             int k) {
+  const int H = g.nx >> 1;
   const size_t c = cidx(g, 2 * m, j, k), sy = (size_t)g.nx, sz = (size_t)g.nx * g.ny;
   const T ix = (T)g.ihx2, iy = (T)g.ihy2, iz = (T)g.ihz2;
   const bool top = k == g.nz - 1, he = m < H - 1, hn = j < g.ny - 1;
@@ -121,8 +122,6 @@ __device__ __forceinline__ void bottom_setup(BottomPair<T>& q, const FaceCoef<T>
   T ys[2] = {co.wy[c], co.wy[c + 1]}, yn[2] = {co.wy[cn], co.wy[cn + 1]};
   T zb[2] = {co.wz[c], co.wz[c + 1]}, zt[2] = {wtp[0], wtp[1]};
   const int par = (j + k) & 1;  // e_0
-  q.at = xoff + p;
-  q.pk = bottom_parent(g, p);
   q.dx = par ? 1 : -1;
   q.wi = xw[1] * ix;
   const T fb = k == 0 ? T(2) : T(1), ft = top ? T(2) : T(1);
@@ -135,8 +134,16 @@ __device__ __forceinline__ void bottom_setup(BottomPair<T>& q, const FaceCoef<T>
     q.wb[cc] = fb * ((e ? zb[1] : zb[0]) * iz);
     q.wt[cc] = ft * ((e ? zt[1] : zt[0]) * iz);
     q.rd[cc] = recip(q.wi + q.wo[cc] + q.ws[cc] + q.wn[cc] + q.wb[cc] + q.wt[cc]);
-    q.b[cc] = T(0);
   }
+}
+
+template <typename T>
+__device__ __forceinline__ void bottom_setup(BottomPair<T>& q, const FaceCoef<T>& co, const Geom& g, int xoff, int p) {
+  const BottomAt at(p, g.nx >> 1, g.ny);
+  pair_weights(q, co, g, at.m, at.j, at.k);
+  q.at = xoff + p;
+  q.pk = bottom_parent(g, p);
+  q.b[0] = q.b[1] = T(0);
 }
 
 // Neighbour values of the pair's colour-C cell (i: the pair's other cell, o:
@@ -146,9 +153,8 @@ struct BottomNbrs {
   T i, o, s, n, b, t;
 };
 
-template <int C, typename T>
-__device__ __forceinline__ BottomNbrs<T> bottom_nbrs(const BottomPair<T>& q, const T (*lx)[BOTTOM_LDS_X], int sy,
-                                                     int sz) {
+template <int C, typename T, int N>
+__device__ __forceinline__ BottomNbrs<T> bottom_nbrs(const BottomPair<T>& q, const T (&lx)[2][N], int sy, int sz) {
   // (opaque: the neighbours' addresses are recomputed in each phase rather
   // than kept in registers)
   int at = q.at;
@@ -157,9 +163,8 @@ __device__ __forceinline__ BottomNbrs<T> bottom_nbrs(const BottomPair<T>& q, con
   return BottomNbrs<T>{p[0], p[C ? -q.dx : q.dx], p[-sy], p[sy], p[-sz], p[sz]};
 }
 
-template <int C, typename T>
-__device__ __forceinline__ void bottom_update(const BottomPair<T>& q, const BottomNbrs<T>& v,
-                                              T (*lx)[BOTTOM_LDS_X]) {
+template <int C, typename T, int N>
+__device__ __forceinline__ void bottom_update(const BottomPair<T>& q, const BottomNbrs<T>& v, T (&lx)[2][N]) {
   const T off = q.wi * v.i + q.wo[C] * v.o + q.ws[C] * v.s + q.wn[C] * v.n + q.wb[C] * v.b + q.wt[C] * v.t;
   lx[C][q.at] = (q.b[C] + off) * q.rd[C];
 }
