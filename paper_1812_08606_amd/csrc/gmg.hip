@@ -312,6 +312,7 @@ struct gmg_ctx {
   bool graphs_broken = false;
   hipStream_t cap_stream = nullptr;  // capture only (the caller's may be the null stream)
   double* pinned;
+  bool mapped;  // pinned is memory the GPU can write (not in fgmres_solve_static)
   hipError_t err;
   Profiler prof;
   // host Givens state
@@ -1459,18 +1460,48 @@ void cycle_any(gmg_ctx* c, const double* u, const double* bscale, void* z, bool 
 // FGMRES pieces.
 // ---------------------------------------------------------------------------
 
-Launch red_launch(gmg_ctx* c) { return col_launch(c->nx, c->ny, c->nz, MAX_RED_BLOCKS); }
+// Column-marching launch with `lanes` lanes per row (cells or x-pairs), rows
+// of BY threads, and z-chunks from the rounds model with four blocks per CU
+// resident (their occupancy): a marching column re-reads a plane at each end
+// of its chunk, and a last round with few blocks leaves CUs idle.  At most
+// MAX_RED_BLOCKS blocks (one partial per block and vector; rows strided
+// beyond).  Measured against 16384 blocks: the operator with its dots 21.6 ->
+// 17.7 us at 128^3, 161 -> 147 at 256^3, 1231 -> 1230 at 512^3 (float32 z,
+// mean over five steps), the initial residual 16.6 -> 12.0, 84 -> 77 and 570
+// -> 555 us, dL/da 120 -> 100 us at 256^3.  (512, 768, 1280 and 1536 blocks
+// were 10 to 30% slower than 1024 somewhere.)
+Launch march_launch(gmg_ctx* c, int lanes) {
+  const int gx = (lanes + BX - 1) / BX;
+  int gy = (c->ny + BY - 1) / BY;
+  if ((long long)gx * gy > MAX_RED_BLOCKS) gy = std::max(1, MAX_RED_BLOCKS / gx);
+  const long long cols = (long long)gx * gy;
+  const int max_gz = (int)std::max<long long>(1, MAX_RED_BLOCKS / cols);
+  const int kc = rounds_kc(c->nz, cols, 4LL * c->cus, (c->nz + max_gz - 1) / max_gz, 2);
+  return Launch{dim3(gx, gy, (c->nz + kc - 1) / kc), dim3(BX, BY, 1), kc};
+}
+Launch red_launch(gmg_ctx* c) { return march_launch(c, c->nx); }
 // the same with one lane per x-pair of the finest level (nx even)
-Launch pair_red_launch(gmg_ctx* c) { return col_launch(c->nx / 2, c->ny, c->nz, MAX_RED_BLOCKS); }
+Launch pair_red_launch(gmg_ctx* c) { return march_launch(c, c->nx / 2); }
 
-void finalize(gmg_ctx* c, int nblocks, int nv, int mode, double* out, const double* scale, double* out2) {
+// host_at >= 0: the results also to c->pinned[host_at ..] where the GPU can
+// write there (fetch then needs no copy: a 2 to 4 us launch less per wait).
+void finalize(gmg_ctx* c, int nblocks, int nv, int mode, double* out, const double* scale, double* out2,
+              int host_at = -1) {
   const Launch one{dim3(1), dim3(FIN_THREADS, 1, 1), 0};
   GMG_LAUNCH(c, "finalize", k_finalize, one, wsp<const double>(c, c->L.partials), nblocks, nv, mode, out, scale,
-             out2);
+             out2, host_at >= 0 && c->mapped ? c->pinned + host_at : (double*)nullptr);
 }
 
-// r0 = b - A x (x may be null), ||b||^2 and ||r0||^2 into misc[0..1],
-// v_1 scale 1/||r0|| into vscale[0]; r0 stored into V[0] when store.
+// Waits for n values at dev, which finalize also sent to c->pinned[0 ..].
+int fetch(gmg_ctx* c, const double* dev, int n) {
+  if (!c->mapped) return read_back(c, dev, n);
+  note(c, hipStreamSynchronize(c->stream));
+  return c->err == hipSuccess ? GMG_OK : GMG_ERR_HIP;
+}
+
+// r0 = b - A x (x may be null), ||b||^2, ||r0||^2 and ||r0|| into misc[0..2]
+// (and to the host), v_1 scale 1/||r0|| into vscale[0]; r0 stored into V[0]
+// when store.
 void init_residual(gmg_ctx* c, const double* f, const double* x, double pb, double pt, bool store) {
   // the pair kernel loads f and x (caller's buffers) as 16-byte vectors
   auto a16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
@@ -1488,16 +1519,17 @@ void init_residual(gmg_ctx* c, const double* f, const double* x, double pb, doub
   else
     GMG_LAUNCH(c, "init_residual", k_init_residual_pair<false>, rl, f, c->a, x, g, pb, pt, r,
                wsp<double>(c, c->L.partials), rl.kc);
-  finalize(c, rl.nblocks(), 2, 0, misc, nullptr, nullptr);
   // misc[2] = ||r0||, vscale[0] = 1/||r0||
-  const Launch one{dim3(1), dim3(FIN_THREADS, 1, 1), 0};
-  GMG_LAUNCH(c, "finalize", k_finalize, one, wsp<const double>(c, c->L.partials) + rl.nblocks(), rl.nblocks(), 1,
-             2, misc + 2, nullptr, scal_vscale(c));
+  finalize(c, rl.nblocks(), 2, FIN_RESID, misc, nullptr, scal_vscale(c), 0);
 }
 
+// Flat reductions: two blocks per CU, each thread striding the vectors (the
+// orthogonalisation at 512^3, mean over seven steps: 1276 us, against 1327
+// with four blocks per CU and 1290-1430 with 16-byte loads; the second stage
+// then adds 512 partials instead of 16384, 11.3 -> 7.3 us).
 // Launches of the vector-count templates (NV = 1..MAXV) through tables.
 Launch red_flat(gmg_ctx* c) {
-  const size_t b = std::min<size_t>((c->N + NTHREADS - 1) / NTHREADS, MAX_RED_BLOCKS);
+  const size_t b = std::min<size_t>((c->N + NTHREADS - 1) / NTHREADS, 2 * (size_t)c->cus);
   return Launch{dim3((unsigned)std::max<size_t>(b, 1)), dim3(BX, BY, 1), 0};
 }
 
@@ -1505,14 +1537,7 @@ Launch red_flat(gmg_ctx* c) {
 // (at least two levels), one cell per thread otherwise; at most
 // MAX_RED_BLOCKS blocks (one partial per block and vector).
 Launch opdot_launch(gmg_ctx* c) {
-  const LevelShape& s = c->L.shapes[0];
-  if (c->L.shapes.size() == 1) return red_launch(c);
-  const int gx = (s.nx / 2 + BX - 1) / BX;
-  int gy = (s.ny + BY - 1) / BY;
-  if ((long long)gx * gy > MAX_RED_BLOCKS) gy = std::max(1, MAX_RED_BLOCKS / gx);  // rows strided
-  const int gz = std::max(1, std::min(s.nz, MAX_RED_BLOCKS / (gx * gy)));
-  const int kc = (s.nz + gz - 1) / gz;
-  return Launch{dim3(gx, gy, (s.nz + kc - 1) / kc), dim3(BX, BY, 1), kc};
+  return c->L.shapes.size() == 1 ? red_launch(c) : march_launch(c, c->nx / 2);
 }
 
 template <typename TZ, int NV>
@@ -1596,10 +1621,10 @@ void arnoldi_step(gmg_ctx* c, int j) {
         opdot_nv<float>(nq, c, rl, (const float*)Zb, w, V, seq);
       else
         opdot_nv<double>(nq, c, rl, (const double*)Zb, w, V, seq);
-      finalize(c, rl.nblocks(), nq, 1, hc + q0, vs + q0, nullptr);
+      finalize(c, rl.nblocks(), nq, FIN_DOTS, hc + q0, vs + q0, nullptr, q0);
     } else {
       dot_nv(nq, c, fl, w, V + (size_t)q0 * N, seq);
-      finalize(c, fl.nblocks(), nq, 1, hc + q0, vs + q0, nullptr);
+      finalize(c, fl.nblocks(), nq, FIN_DOTS, hc + q0, vs + q0, nullptr, q0);
     }
   }
   for (int q0 = 0; q0 < nv; q0 += MAXV) {
@@ -1607,7 +1632,7 @@ void arnoldi_step(gmg_ctx* c, int j) {
     const int last = q0 + nq >= nv;
     axpy_nv(nq, c, fl, w, V + (size_t)q0 * N, hc + q0, vs + q0, last, seq);
   }
-  finalize(c, fl.nblocks(), 1, 2, hc + (j + 1), nullptr, vs + (j + 1));
+  finalize(c, fl.nblocks(), 1, FIN_NORM, hc + (j + 1), nullptr, vs + (j + 1), j + 1);
 }
 
 // phi += sum_{i<k} y_i z_i
@@ -1813,12 +1838,12 @@ void cheb_step(gmg_ctx* c, int l, double* hcol, double* vs) {
     GMG_LAUNCH(c, "cheb_convert_dots", (k_convert_dots<T, NV>), rf, (const T*)E, w, n, U, c->L.ldv, part);
     nb = rf.nblocks();
   }
-  finalize(c, nb, NV, 1, hcol, vs, nullptr);
+  finalize(c, nb, NV, FIN_DOTS, hcol, vs, nullptr);
   Launch rf = flat_launch(n);
   rf.grid.x = std::min<unsigned>(rf.grid.x, MAX_RED_BLOCKS);
   GMG_LAUNCH(c, "axpy_norm", k_axpy_norm<NV>, rf, w, n, U, c->L.ldv, (const double*)hcol, (const double*)vs, 1,
              part);
-  finalize(c, rf.nblocks(), 1, 2, hcol + NV, nullptr, vs + NV);
+  finalize(c, rf.nblocks(), 1, FIN_NORM, hcol + NV, nullptr, vs + NV);
 }
 
 template <typename T, size_t... I>
@@ -1849,7 +1874,7 @@ int cheb_estimate(gmg_ctx* c) {
     GMG_LAUNCH(c, "uniform_start", k_uniform_start, fl, V0, n, (unsigned long long)l);
     GMG_LAUNCH(c, "multidot", k_multidot<1>, rf, (const double*)V0, n, (const double*)V0, c->L.ldv,
                wsp<double>(c, c->L.partials));
-    finalize(c, rf.nblocks(), 1, 2, Sl + CHEB_NORM0, nullptr, vs);
+    finalize(c, rf.nblocks(), 1, FIN_NORM, Sl + CHEB_NORM0, nullptr, vs);
     for (int j = 0; j < CHEB_ARNOLDI; ++j)
       cheb_step_nv<T>(j + 1, c, l, Sl + (size_t)j * (CHEB_ARNOLDI + 1), vs, seq);
   }
@@ -1924,7 +1949,7 @@ void lincomb(gmg_ctx* c, double* y, const double* x0, double c0, const double* x
   const Launch fl = red_flat(c);
   GMG_LAUNCH(c, "lincomb", k_lincomb3, fl, y, x0, x1, x2, c0, c1, c2, c->N, norm2 ? 1 : 0,
              wsp<double>(c, c->L.partials));
-  if (norm2) finalize(c, fl.nblocks(), 1, 0, norm2, nullptr, nullptr);
+  if (norm2) finalize(c, fl.nblocks(), 1, FIN_SUM, norm2, nullptr, nullptr, (int)(norm2 - kscal(c)));
 }
 
 // (w, u_q) for nv (1 or 2) vectors u_q at stride ldv from U, into out (device).
@@ -1934,7 +1959,7 @@ void kdots(gmg_ctx* c, const double* w, const double* U, int nv, double* out) {
     launch_dot<1>(c, fl, w, U);
   else
     launch_dot<2>(c, fl, w, U);
-  finalize(c, fl.nblocks(), nv, 0, out, nullptr, nullptr);
+  finalize(c, fl.nblocks(), nv, FIN_SUM, out, nullptr, nullptr, (int)(out - kscal(c)));
 }
 
 // w = A x (homogeneous plates) with the dots (w, u_q), q < nv (1 or 2), into out.
@@ -1952,7 +1977,7 @@ void kapply(gmg_ctx* c, const double* x, double* w, const double* U, int nv, dou
     GMG_LAUNCH(c, "op_natural", k_op_natural<1>, rl, x, one, c->a, g, w, U, c->L.ldv, part, rl.kc);
   else
     GMG_LAUNCH(c, "op_natural", k_op_natural<2>, rl, x, one, c->a, g, w, U, c->L.ldv, part, rl.kc);
-  finalize(c, rl.nblocks(), nv, 0, out, nullptr, nullptr);
+  finalize(c, rl.nblocks(), nv, FIN_SUM, out, nullptr, nullptr, (int)(out - kscal(c)));
 }
 
 // GMRES solution update: u = sum_i y_i v_i (v_i = vscale_i V_i) into the
@@ -2001,7 +2026,7 @@ struct KrylovOut {
 // r = b - A x into V[0] (x null: x = 0), ||b|| and ||r|| on the host.
 int true_residual(gmg_ctx* c, const double* f, const double* x, double pb, double pt, double& bnorm, double& rnorm) {
   init_residual(c, f, x, pb, pt, true);
-  if (read_back(c, scal_misc(c), 3) != GMG_OK) return GMG_ERR_HIP;
+  if (fetch(c, scal_misc(c), 3) != GMG_OK) return GMG_ERR_HIP;
   bnorm = std::sqrt(c->pinned[0]);
   rnorm = c->pinned[2];
   if (!std::isfinite(bnorm) || !std::isfinite(rnorm)) return GMG_ERR_NONFINITE;
@@ -2037,24 +2062,24 @@ int krylov_cg(gmg_ctx* c, const double* f, double pb, double pt, double tol, dou
     precond_natural(c, r, z);
     lincomb(c, p, z, 1.0, nullptr, 0.0, nullptr, 0.0, nullptr);
     kdots(c, z, r, 1, s);  // rho = (r, z)
-    if (read_back(c, s, 1) != GMG_OK) return GMG_ERR_HIP;
+    if (fetch(c, s, 1) != GMG_OK) return GMG_ERR_HIP;
     double rho = c->pinned[0];
     while (out.it < max_iter) {
       kapply(c, p, q, p, 1, s);  // q = A p, (q, p)
-      if (read_back(c, s, 1) != GMG_OK) return GMG_ERR_HIP;
+      if (fetch(c, s, 1) != GMG_OK) return GMG_ERR_HIP;
       const double pq = c->pinned[0];
       if (!std::isfinite(pq) || pq == 0.0) return GMG_ERR_BREAKDOWN;
       const double alpha = rho / pq;
       lincomb(c, x, x, 1.0, p, alpha, nullptr, 0.0, nullptr);
       lincomb(c, r, r, 1.0, q, -alpha, nullptr, 0.0, s);
       ++out.it;
-      if (read_back(c, s, 1) != GMG_OK) return GMG_ERR_HIP;
+      if (fetch(c, s, 1) != GMG_OK) return GMG_ERR_HIP;
       const double rr = std::sqrt(c->pinned[0]);
       if (!std::isfinite(rr)) return GMG_ERR_NONFINITE;
       if (rr < tol * bnorm) break;
       precond_natural(c, r, z);
       kdots(c, z, r, 2, s);  // (z, r), (z, q): r and q are adjacent slots
-      if (read_back(c, s, 2) != GMG_OK) return GMG_ERR_HIP;
+      if (fetch(c, s, 2) != GMG_OK) return GMG_ERR_HIP;
       const double rho_new = c->pinned[0];
       const double beta = flexible ? -c->pinned[1] / pq : rho_new / rho;
       lincomb(c, p, z, 1.0, p, beta, nullptr, 0.0, nullptr);
@@ -2085,7 +2110,7 @@ int krylov_cgs(gmg_ctx* c, const double* f, double pb, double pt, double tol, do
     while (out.it < max_iter) {
       precond_natural(c, p, mh);
       kapply(c, mh, v, rs, 1, s);  // v = A M p, (v, r~)
-      if (read_back(c, s, 1) != GMG_OK) return GMG_ERR_HIP;
+      if (fetch(c, s, 1) != GMG_OK) return GMG_ERR_HIP;
       const double sigma = c->pinned[0];
       if (!std::isfinite(sigma) || sigma == 0.0) return GMG_ERR_BREAKDOWN;
       const double alpha = rho / sigma;
@@ -2097,7 +2122,7 @@ int krylov_cgs(gmg_ctx* c, const double* f, double pb, double pt, double tol, do
       lincomb(c, r, r, 1.0, w, -alpha, nullptr, 0.0, s + 1);
       kdots(c, r, rs, 1, s + 2);  // rho' = (r, r~)
       ++out.it;
-      if (read_back(c, s, 3) != GMG_OK) return GMG_ERR_HIP;
+      if (fetch(c, s, 3) != GMG_OK) return GMG_ERR_HIP;
       const double rr = std::sqrt(c->pinned[1]), rho_new = c->pinned[2];
       if (!std::isfinite(rr)) return GMG_ERR_NONFINITE;
       if (rr < tol * bnorm) break;
@@ -2134,12 +2159,12 @@ int krylov_bicgstab(gmg_ctx* c, const double* f, double pb, double pt, double to
       lincomb(c, p, r, 1.0, p, beta, v, -beta * omega, nullptr);
       precond_natural(c, p, ph);
       kapply(c, ph, v, rs, 1, s);  // v = A M p, (v, r~)
-      if (read_back(c, s, 1) != GMG_OK) return GMG_ERR_HIP;
+      if (fetch(c, s, 1) != GMG_OK) return GMG_ERR_HIP;
       const double rv = c->pinned[0];
       if (!std::isfinite(rv) || rv == 0.0) return GMG_ERR_BREAKDOWN;
       alpha = rho_new / rv;
       lincomb(c, sv, r, 1.0, v, -alpha, nullptr, 0.0, s);
-      if (read_back(c, s, 1) != GMG_OK) return GMG_ERR_HIP;
+      if (fetch(c, s, 1) != GMG_OK) return GMG_ERR_HIP;
       if (std::sqrt(c->pinned[0]) < tol * bnorm) {  // converged half-way
         lincomb(c, x, x, 1.0, ph, alpha, nullptr, 0.0, nullptr);
         lincomb(c, r, sv, 1.0, nullptr, 0.0, nullptr, 0.0, nullptr);
@@ -2149,7 +2174,7 @@ int krylov_bicgstab(gmg_ctx* c, const double* f, double pb, double pt, double to
       precond_natural(c, sv, sh);
       kapply(c, sh, t, sv, 1, s);  // t = A M s, (t, s)
       kdots(c, t, t, 1, s + 1);   // (t, t)
-      if (read_back(c, s, 2) != GMG_OK) return GMG_ERR_HIP;
+      if (fetch(c, s, 2) != GMG_OK) return GMG_ERR_HIP;
       const double ts = c->pinned[0], tt = c->pinned[1];
       if (!std::isfinite(tt) || tt == 0.0) return GMG_ERR_BREAKDOWN;
       omega = ts / tt;
@@ -2157,7 +2182,7 @@ int krylov_bicgstab(gmg_ctx* c, const double* f, double pb, double pt, double to
       lincomb(c, r, sv, 1.0, t, -omega, nullptr, 0.0, s);
       kdots(c, r, rs, 1, s + 1);
       ++out.it;
-      if (read_back(c, s, 2) != GMG_OK) return GMG_ERR_HIP;
+      if (fetch(c, s, 2) != GMG_OK) return GMG_ERR_HIP;
       const double rr = std::sqrt(c->pinned[0]);
       if (!std::isfinite(rr)) return GMG_ERR_NONFINITE;
       rho = rho_new;
@@ -2205,7 +2230,7 @@ namespace {
 // host_buf of MAX_RESTART + 8 doubles for read-backs; builds the hierarchy.
 int init_ctx(gmg_ctx* c, int nx, int ny, int nz, double hx, double hy, double hz, const double* a_dev,
              const gmg_options* opt, void* ws, size_t ws_bytes, void* hip_stream, const Layout& L,
-             double* host_buf) {
+             double* host_buf, bool mapped) {
   c->nx = nx;
   c->ny = ny;
   c->nz = nz;
@@ -2227,6 +2252,7 @@ int init_ctx(gmg_ctx* c, int nx, int ny, int nz, double hx, double hy, double hz
       (opt->smoother == GMG_SMOOTH_CHEBYSHEV || opt->restriction == GMG_RESTRICT_TRANSPOSE) ? -1 : bottom_level(L);
   c->err = hipSuccess;
   c->pinned = host_buf;
+  c->mapped = mapped;
   {
     int dev = 0, n = 0;
     c->cus = hipGetDevice(&dev) == hipSuccess &&
@@ -2279,7 +2305,7 @@ int gmg_setup(int nx, int ny, int nz, double hx, double hy, double hz, const dou
     return GMG_ERR_HIP;
   }
   const int r = init_ctx(c, nx, ny, nz, hx, hy, hz, a_dev, opt, workspace_dev, workspace_bytes, hip_stream, L,
-                         pinned);
+                         pinned, true);
   if (r != GMG_OK) {
     gmg_destroy(c);
     return r;
@@ -2369,7 +2395,7 @@ int fgmres_core(gmg_ctx* c, const double* f_dev, double phi_bot, double phi_top,
   while (true) {
     // r_0 = b - A x_0 into V[0] (the true residual at every restart)
     init_residual(c, f_dev, (first && !use_x0) ? nullptr : phi_dev, phi_bot, phi_top, !likely_last);
-    if (read_back(c, misc, 3) != GMG_OK) return finish(GMG_ERR_HIP, NAN);
+    if (fetch(c, misc, 3) != GMG_OK) return finish(GMG_ERR_HIP, NAN);
     const double bn2 = c->pinned[0];
     double beta = c->pinned[2];
     if (!std::isfinite(bn2) || !std::isfinite(beta)) return finish(GMG_ERR_NONFINITE, NAN);
@@ -2390,7 +2416,7 @@ int fgmres_core(gmg_ctx* c, const double* f_dev, double phi_bot, double phi_top,
     if (likely_last) {
       // (the same kernel and reduction: the same norms)
       init_residual(c, f_dev, phi_dev, phi_bot, phi_top, true);
-      if (read_back(c, misc, 3) != GMG_OK) return finish(GMG_ERR_HIP, NAN);
+      if (fetch(c, misc, 3) != GMG_OK) return finish(GMG_ERR_HIP, NAN);
       beta = c->pinned[2];
     }
     likely_last = false;
@@ -2401,7 +2427,7 @@ int fgmres_core(gmg_ctx* c, const double* f_dev, double phi_bot, double phi_top,
     for (int j = 0; j < m; ++j) {
       if (it >= c->opt.max_iter) break;
       arnoldi_step(c, j);
-      if (read_back(c, scal_hcol(c, j), j + 2) != GMG_OK) return finish(GMG_ERR_HIP, NAN);
+      if (fetch(c, scal_hcol(c, j), j + 2) != GMG_OK) return finish(GMG_ERR_HIP, NAN);
       std::vector<double> h(c->pinned, c->pinned + j + 2);
       double colnorm = 0.0;
       for (double v : h) {
@@ -2518,7 +2544,8 @@ int fgmres_solve_static(int nx, int ny, int nz, double hx, double hy, double hz,
   std::lock_guard<std::mutex> g(g_scratch_mu[dev]);
   double host_buf[MAX_RESTART + 8];
   gmg_ctx c;
-  st = init_ctx(&c, nx, ny, nz, hx, hy, hz, a_dev, opt, ws, GMG_STATIC_SCRATCH_BYTES, hip_stream, L, host_buf);
+  st = init_ctx(&c, nx, ny, nz, hx, hy, hz, a_dev, opt, ws, GMG_STATIC_SCRATCH_BYTES, hip_stream, L, host_buf,
+                false);
   if (st == GMG_OK)
     st = fgmres_solve(&c, f_dev, phi_bot, phi_top, tol, phi_dev, use_x0, iterations, res_hist, res_hist_cap,
                       res_hist_len, final_true_relres);
@@ -2579,8 +2606,7 @@ int gmg_apply_operator(gmg_ctx* c, const double* x_dev, double* y_dev, double ph
   if (!valid_ctx(c) || !x_dev || !y_dev) return GMG_ERR_ARG;
   auto a16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
   if (c->nx % 2 == 0 && a16(x_dev) && a16(c->a) && a16(y_dev)) {  // pairs are 16-byte loads and stores
-    // (z-chunks from 4 to 64 planes were within 6% of each other from 128^3 to 512^3)
-    const Launch lp = pair_launch(c->nx, c->ny, c->nz, 4096, 8, 2);
+    const Launch lp = march_launch(c, c->nx / 2);
     GMG_LAUNCH(c, "apply_bc", k_apply_bc_pair, lp, x_dev, c->a, c->L.shapes[0].geom(), phi_bot, phi_top, y_dev, lp.kc);
     note(c, hipStreamSynchronize(c->stream));
     return c->err == hipSuccess ? GMG_OK : GMG_ERR_HIP;
@@ -2635,7 +2661,7 @@ int gmg_face_flux_grad(gmg_ctx* c, const double* phi_dev, const double* lam_dev,
   if (!valid_ctx(c) || !phi_dev || !lam_dev || !dLda_dev) return GMG_ERR_ARG;
   auto a16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
   if (c->nx % 2 == 0 && a16(phi_dev) && a16(lam_dev) && a16(dLda_dev)) {
-    const Launch lc = col_launch(c->nx / 2, c->ny, c->nz, 1 << 16);
+    const Launch lc = march_launch(c, c->nx / 2);
     GMG_LAUNCH(c, "face_grad", k_face_grad_pair, lc, phi_dev, lam_dev, c->L.shapes[0].geom(), phi_bot, phi_top,
                dLda_dev, lc.kc);
   } else {

@@ -758,16 +758,22 @@ __global__ __launch_bounds__(NTHREADS) void k_update(double* __restrict__ phi, s
 }
 
 // Second reduction stage, one block: sum the per-block partials of nv
-// vectors in a fixed order.  mode 0: out[v] = sum; mode 1: out[v] = sum *
-// scale[v] (dots against lazily normalised vectors); mode 2 (nv = 1):
-// out[0] = sqrt(sum), out2[0] = 1 / sqrt(sum) (0 if the sum is 0).
+// vectors in a fixed order.
+//   FIN_SUM    out[v] = sum
+//   FIN_DOTS   out[v] = sum * scale[v] (dots against lazily normalised vectors)
+//   FIN_NORM   (nv = 1) out[0] = sqrt(sum), out2[0] = 1 / sqrt(sum) (0 if the
+//              sum is 0)
+//   FIN_RESID  (nv = 2) out[0], out[1] the sums, out[2] = sqrt of the second,
+//              out2[0] its inverse (0 if it is 0)
+// The results also go to host (pinned host memory) when it is given.
+enum { FIN_SUM = 0, FIN_DOTS = 1, FIN_NORM = 2, FIN_RESID = 3 };
 constexpr int FIN_THREADS = 1024;
 constexpr int FIN_BATCH = 8;  // partials of one vector a thread loads per wait
 
 __global__ __launch_bounds__(FIN_THREADS) void k_finalize(const double* __restrict__ partials, int nblocks, int nv,
                                                           int mode, double* __restrict__ out,
                                                           const double* __restrict__ scale,
-                                                          double* __restrict__ out2) {
+                                                          double* __restrict__ out2, double* __restrict__ host) {
   __shared__ double sm[MAXV][FIN_THREADS / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // vector by vector, each thread adds its partials b = tid, tid +
@@ -795,14 +801,15 @@ __global__ __launch_bounds__(FIN_THREADS) void k_finalize(const double* __restri
   if (tid < nv) {
     double t = 0.0;
     for (int w = 0; w < FIN_THREADS / 64; ++w) t += sm[tid][w];
-    if (mode == 0) {
-      out[tid] = t;
-    } else if (mode == 1) {
-      out[tid] = t * scale[tid];
-    } else {
-      const double r = sqrt(t);
-      out[0] = r;
-      out2[0] = r > 0.0 ? 1.0 / r : 0.0;
+    const double r = mode == FIN_DOTS ? t * scale[tid] : mode == FIN_NORM ? sqrt(t) : t;
+    out[tid] = r;
+    if (host) host[tid] = r;
+    if (mode == FIN_NORM) out2[0] = r > 0.0 ? 1.0 / r : 0.0;
+    if (mode == FIN_RESID && tid == 1) {
+      const double n = sqrt(t);
+      out[2] = n;
+      if (host) host[2] = n;
+      out2[0] = n > 0.0 ? 1.0 / n : 0.0;
     }
   }
 }
