@@ -122,8 +122,9 @@ typedef struct gmg_options {
                            x-pairs in float32, 128 in float64; half-sweeps
                            elsewhere);
                            GMG_SWEEP_AUTO (default): fused where it was
-                           measured faster (finest level: long z-chunks;
-                           coarse levels: at least 128^3 cells), and on levels
+                           measured faster (finest level: by row length and
+                           size, about 144^3 cells and up; coarse levels:
+                           at least 128^3 cells), and on levels
                            whose iterate has at most 4 MiB several sweeps per
                            kernel, with the interpolation or the residual
                            restriction in it (nu_pre, nu_post >= 1, mean

@@ -25,6 +25,7 @@
 #include "gmg_krylov.hpp"
 #include "gmg_cheb.hpp"
 #include "gmg_face_sym.hpp"
+#include "gmg_sym_row.hpp"
 
 using namespace gmg;
 
@@ -294,6 +295,7 @@ struct gmg_ctx {
     int tx, ty, tz, hx, hy;
   };
   std::vector<std::array<std::vector<LegPlan>, 3>> legs;  // per level: pre from zero, pre from a guess, post
+  int fine_form;    // FINE_*: kernels of the finest level's smoothing
   bool fmg_now;     // the running solve preconditions with full multigrid cycles
   bool gmres_mode;  // GMRES: one preconditioned-vector slot, x updated by M (V y)
   int nprec;        // preconditioner applications of the running solve
@@ -518,34 +520,36 @@ Launch pair_launch(int nx, int ny, int nz, long long target, int min_kc, int tri
 }
 
 // z-chunk of a column-marching launch with `cols` blocks per chunk column
-// and `resident` blocks running at once: the chunk (at least min_kc planes)
-// that minimises the rounds of blocks times the planes a block marches (its
-// chunk plus `extra`), the smallest chunk for each chunk count, among
-// chunks that give at least min_rounds rounds when any does.  (A round
-// with few blocks leaves most CUs idle: at level 1 of the 512^3 grid,
-// 11-plane chunks made 1032 blocks of one per CU, 4.03 rounds on 256 CUs;
-// 24-plane chunks, 473 blocks in 2 rounds, took 110.5 us per sweep against
-// 137.8.  The finest level's fused sweep was slower in 3 long rounds than
-// in 8 short ones, 563 against 507 us, at the same modelled cost: it keeps
-// at least 4.)
-inline int rounds_kc(int nz, long long cols, long long resident, int min_kc, int extra, int min_rounds = 1) {
-  int best = std::min(nz, min_kc), best_any = best;
-  double best_cost = 1e300, best_cost_any = 1e300;
-  for (int kc = std::min(nz, min_kc); kc <= nz; ++kc) {
+// and `resident` blocks running at once: the chunk (at least min_kc planes, a
+// multiple of step) that minimises the rounds of blocks times the planes a
+// block marches (its chunk plus `extra`), the smallest chunk for each chunk
+// count, among chunks that give at least min_rounds rounds when any does; and
+// that product.  (A round with few blocks leaves most CUs idle: at level 1 of
+// the 512^3 grid, 11-plane chunks made 1032 blocks of one per CU, 4.03 rounds
+// on 256 CUs; 24-plane chunks, 473 blocks in 2 rounds, took 110.5 us per sweep
+// against 137.8.  An even chunk is chosen as such: rounding the best chunk
+// down instead made 2 rounds of 1, 285 us against 166 for the fused residual
+// sweep at 320^3.)
+struct Rounds {
+  int kc;
+  double planes;
+};
+inline Rounds rounds_of(int nz, long long cols, long long resident, int min_kc, int extra, int min_rounds = 1,
+                        int step = 1) {
+  const int first = std::max(step, (std::min(nz, min_kc) + step - 1) / step * step);
+  Rounds best{first, 1e300}, any{first, 1e300};
+  for (int kc = first; kc < nz + step; kc += step) {
     const long long gz = (nz + kc - 1) / kc;
-    if (kc > 1 && kc > min_kc && (nz + kc - 2) / (kc - 1) == gz) continue;  // a smaller chunk gives the same count
+    if (kc > first && (nz + kc - step - 1) / (kc - step) == gz) continue;  // a smaller chunk gives the same count
     const long long rounds = (cols * gz + resident - 1) / resident;
     const double cost = (double)rounds * (kc + extra);
-    if (cost < best_cost_any) {
-      best_cost_any = cost;
-      best_any = kc;
-    }
-    if (rounds >= min_rounds && cost < best_cost) {
-      best_cost = cost;
-      best = kc;
-    }
+    if (cost < any.planes) any = {kc, cost};
+    if (rounds >= min_rounds && cost < best.planes) best = {kc, cost};
   }
-  return best_cost < 1e300 ? best : best_any;
+  return best.planes < 1e300 ? best : any;
+}
+inline int rounds_kc(int nz, long long cols, long long resident, int min_kc, int extra, int min_rounds = 1) {
+  return std::min(nz, rounds_of(nz, cols, resident, min_kc, extra, min_rounds).kc);
 }
 
 // Waves per row of the coarse levels' fused sweep (a block spans the row),
@@ -579,7 +583,8 @@ bool fused_face(gmg_ctx* c, int l) {
 // One fused symmetric sweep on coarse level l: colour c1 from Xin into Xout,
 // then the other colour from the new values (FIRST: from x = 0, Xin unused).
 // A block spans the row (one to four waves) and FaceSymShape's rows; z-chunks
-// of at least 8 planes from the rounds model (rounds_kc).
+// of at least 4 planes from the rounds model (rounds_kc; with 8, the 128^3
+// level's 160 blocks left 96 CUs idle: 21.8 against 18.9 us per sweep).
 template <typename T, bool FIRST>
 void sym_face(gmg_ctx* c, int l, const T* Xin, T* Xout, const T* b, const FaceCoef<T>& co, int c1) {
   const LevelShape& s = c->L.shapes[l];
@@ -597,7 +602,7 @@ void sym_face(gmg_ctx* c, int l, const T* Xin, T* Xout, const T* b, const FaceCo
                  ? nb
                  : 1;
     }();
-    const int kc = rounds_kc(s.nz, gy, (long long)per_cu * c->cus, 8, 2);
+    const int kc = rounds_kc(s.nz, gy, (long long)per_cu * c->cus, 4, 2);
     const Launch fl{dim3(1, gy, (s.nz + kc - 1) / kc), dim3(64 * WX, R, 1), kc};
     GMG_LAUNCH(c, nm, (k_sym_face<T, FIRST, WX>), fl, Xin, Xout, b, co, s.geom(), kc, c1);
   };
@@ -1175,25 +1180,24 @@ inline long long sym_max_planes(const LevelShape& s) {
 }
 
 // Launch of the fused symmetric sweep on the finest level: blocks of 64 x R
-// threads, about 2048 * 1024 threads in all, z-chunks of at least 8 planes
-// (even with the fused residual restriction: a chunk holds whole coarse
-// planes) and at most sym_max_planes - 8 (a block reads up to three planes
-// below its chunk and four above).
+// threads, z-chunks of at least 8 planes (even with the fused residual
+// restriction: a chunk holds whole coarse planes) from the rounds model and at
+// most sym_max_planes - 8 (a block reads up to three planes below its chunk
+// and four above).  Beyond 2^26 cells at least 4 rounds: at 512^3 the float32
+// sweep took 563 us in 3 long rounds against 507 in 8 short ones at the same
+// modelled cost, while at 208^3 one round takes 33 us and four 50.
 template <typename T, bool RESID = false>
-int sym_default_kc(const LevelShape& s) {
+Rounds sym_rounds(const LevelShape& s, long long resident) {
   using S = SymShape<T, RESID>;
   const int gx = (s.nx / 2 + S::IX - 1) / S::IX, gy = (s.ny + S::IY - 1) / S::IY;
-  const long long target = 2048LL * 1024 / (S::SX * S::R);
-  return (int)std::min<long long>(s.nz, std::max<long long>(8, (s.nz * (long long)gx * gy + target - 1) / target));
+  return rounds_of(s.nz, (long long)gx * gy, resident, 8, RESID ? 3 : 2, s.n() > ((size_t)1 << 26) ? 4 : 1,
+                   RESID ? 2 : 1);
 }
-// The launch takes the chunk from the rounds model (rounds_kc) over the
-// blocks resident at once; `resident` = 0 keeps sym_default_kc.
 template <typename T, bool RESID = false>
-Launch sym_launch(const LevelShape& s, long long resident = 0) {
+Launch sym_launch(const LevelShape& s, long long resident) {
   using S = SymShape<T, RESID>;
   const int gx = (s.nx / 2 + S::IX - 1) / S::IX, gy = (s.ny + S::IY - 1) / S::IY;
-  long long kc = resident > 0 ? rounds_kc(s.nz, (long long)gx * gy, resident, 8, RESID ? 3 : 2, 4)
-                              : sym_default_kc<T, RESID>(s);
+  long long kc = sym_rounds<T, RESID>(s, resident).kc;
   kc = std::min<long long>({kc, s.nz, std::max<long long>(1, sym_max_planes(s) - 8)});
   if (RESID) kc = std::max<long long>(2, kc & ~1LL);
   return Launch{dim3(gx, gy, (unsigned)((s.nz + kc - 1) / kc)), dim3(S::SX, S::R, 1), (int)kc};
@@ -1239,6 +1243,42 @@ void sym_split(gmg_ctx* c, const T* Xin, T* Xout, T* B, const double* u, const d
   }
 }
 
+// Waves per row of k_sym_row (rows of at most 128 pairs), its launch and the
+// planes its rounds march (one block per CU); chunks of at least 4 planes.
+inline int sym_row_waves(const LevelShape& s) { return (s.nx / 2 + 63) / 64; }
+template <typename T>
+Rounds sym_row_rounds(const LevelShape& s, long long resident) {
+  const int iy = (sizeof(T) == 4 ? 16 : 12) / sym_row_waves(s) - 2;
+  return rounds_of(s.nz, (s.ny + iy - 1) / iy, resident, 4, 2);
+}
+template <typename T, bool FIRST, bool SCALED, int WX>
+void launch_sym_row(gmg_ctx* c, const T* Xin, T* Xout, T* B, const double* u, const double* bscale, const T* a,
+                    int c1) {
+  const LevelShape& s = c->L.shapes[0];
+  using S = SymRowShape<T, WX>;
+  const int kc = (int)std::min<long long>(
+      {s.nz, sym_row_rounds<T>(s, c->cus).kc, std::max<long long>(1, sym_max_planes(s) - 8)});
+  const Launch l{dim3(1, (s.ny + S::IY - 1) / S::IY, (s.nz + kc - 1) / kc), dim3(S::SX, S::R, 1), kc};
+  GMG_LAUNCH(c, kname(FIRST ? "sym_row_first" : "sym_row", 0, sizeof(T)), (k_sym_row<T, FIRST, SCALED, WX>), l, Xin,
+             Xout, B, u, bscale, a, s.geom(), c->L.hn, kc, c1);
+}
+template <typename T, bool FIRST>
+void sym_row(gmg_ctx* c, const T* Xin, T* Xout, T* B, const double* u, const double* bscale, const T* a, int c1) {
+  const bool two = sym_row_waves(c->L.shapes[0]) == 2;
+  if (FIRST && bscale) {
+    if (two)
+      launch_sym_row<T, FIRST, true, 2>(c, Xin, Xout, B, u, bscale, a, c1);
+    else
+      launch_sym_row<T, FIRST, true, 1>(c, Xin, Xout, B, u, bscale, a, c1);
+  } else if (two) {
+    launch_sym_row<T, FIRST, false, 2>(c, Xin, Xout, B, u, bscale, a, c1);
+  } else {
+    launch_sym_row<T, FIRST, false, 1>(c, Xin, Xout, B, u, bscale, a, c1);
+  }
+}
+
+enum { FINE_HALF = 0, FINE_SPLIT = 1, FINE_ROW = 2 };
+
 // Buffer of sweep p (1-based; p = 0 the guess) of vcycle_fine_sym: the
 // sweeps ping-pong between the scratch iterate and z so that the last one
 // lands in z.
@@ -1264,8 +1304,9 @@ void vcycle_fine_sym(gmg_ctx* c, const double* u, const double* bscale, T* Z, bo
   // 0.45 ms for the sweep and k_resid_restrict_split.  In float64 the fused
   // kernel's histories need 200 registers, which leaves 8-row blocks owning
   // 4 rows: 1.95 ms against 0.96 + 0.85 ms, so float64 keeps the two kernels.
+  const bool row = c->fine_form == FINE_ROW;
   const bool fuse_resid =
-      sizeof(T) == 4 && c->opt.restriction == GMG_RESTRICT_MEAN && (from_x || npre >= 2);
+      sizeof(T) == 4 && !row && c->opt.restriction == GMG_RESTRICT_MEAN && (from_x || npre >= 2);
   T* bc = wsp<T>(c, c->L.lv[1].b);
   auto sweep = [&](int p) {
     if constexpr (sizeof(T) == 4) {
@@ -1274,10 +1315,15 @@ void vcycle_fine_sym(gmg_ctx* c, const double* u, const double* bscale, T* Z, bo
         return;
       }
     }
-    sym_split<T, false>(c, buf(p - 1), buf(p), B, nullptr, nullptr, a, 0);
+    if (row)
+      sym_row<T, false>(c, buf(p - 1), buf(p), B, nullptr, nullptr, a, 0);
+    else
+      sym_split<T, false>(c, buf(p - 1), buf(p), B, nullptr, nullptr, a, 0);
   };
   if (from_x)
     sweep(1);
+  else if (row)
+    sym_row<T, true>(c, nullptr, buf(1), B, u, bscale, a, 0);
   else
     sym_split<T, true>(c, nullptr, buf(1), B, u, bscale, a, 0);
   for (int p = 2; p <= npre; ++p) sweep(p);
@@ -1290,26 +1336,49 @@ void vcycle_fine_sym(gmg_ctx* c, const double* u, const double* bscale, T* Z, bo
                (const T*)wsp<T>(c, c->L.lv[1].x), s.geom(), hn, 1, l.kc,
                (const T*)nullptr);
   }
-  for (int p = npre + 1; p <= L; ++p) sym_split<T, false>(c, buf(p - 1), buf(p), B, nullptr, nullptr, a, 1);
+  for (int p = npre + 1; p <= L; ++p) {
+    if (row)
+      sym_row<T, false>(c, buf(p - 1), buf(p), B, nullptr, nullptr, a, 1);
+    else
+      sym_split<T, false>(c, buf(p - 1), buf(p), B, nullptr, nullptr, a, 1);
+  }
 }
 
-// Fused symmetric sweeps on the finest level (both smoothing phases
-// present): on request, or by default when their z-chunks are long.  Each
-// chunk of the fused sweep adds two planes of first-colour work and a
-// pipeline fill, so it only wins with chunks of 16 planes or more (measured,
-// solve with full multigrid cycles, V(2,3), mixed / float64: 2% / 6% faster
-// at 384^3 with 21-22-plane chunks, 10% / 12% at 512^3, 9% / 13% at 768^3;
-// 13% / 4% slower at 256^3 with 8-plane chunks).
+// The form of the finest level's smoothing: half-sweeps, or one of the fused
+// symmetric sweeps (both smoothing phases present).  On request k_sym_split;
+// by default the one whose smoothing and residual restriction of one V-cycle
+// the model below finds the shortest (us): a launch and the planes its rounds
+// march, or the lanes of the half-sweeps' 64-pair tiles (the row length
+// decides: tiles of 62 and 60 pairs for k_sym_split, whole rows for
+// k_sym_row).  Measured, solve of five full multigrid cycles V(2,2),
+// half-sweeps / k_sym_split / k_sym_row, ms: float32 128^3 1.61 / 1.64 / 1.57,
+// 160^3 2.51 / 2.35 / 2.40, 208^3 3.70 / 3.40 / 3.53, 256^3 5.47 / 5.73 / 5.43,
+// 256 x 256 x 320 6.90 / 6.92 / 6.69, 288^3 8.80 / 7.83 / -, 384^3 17.6 / 15.6
+// / -; float64 128^3 2.03 / 2.12 / 2.01, 192^3 4.50 / 4.25 / 4.34, 256^3 8.94 /
+// 8.47 / 7.80, 256 x 256 x 320 11.1 / 10.4 / 9.5, 320^3 18.3 / 16.3 / -.
 template <typename T>
-bool sym_chosen(gmg_ctx* c) {
-  const int fs = c->opt.fine_sweep;
-  return c->L.shapes.size() > 1 && sym_max_planes(c->L.shapes[0]) >= 10 &&
-         (fs == GMG_SWEEP_FUSED || (fs == GMG_SWEEP_AUTO && sym_default_kc<T>(c->L.shapes[0]) >= 16));
+int choose_fine_form(gmg_ctx* c) {
+  constexpr bool F32 = sizeof(T) == 4;
+  const LevelShape& s = c->L.shapes[0];
+  const int npre = c->opt.nu_pre, npost = c->opt.nu_post, fs = c->opt.fine_sweep;
+  if (c->L.shapes.size() < 2 || sym_max_planes(s) < 10 || fs == GMG_SWEEP_HALF) return FINE_HALF;
+  if (fs == GMG_SWEEP_FUSED) return FINE_SPLIT;
+  const double lanes = 64.0 * ((s.nx / 2 + 63) / 64) * s.ny * s.nz;  // of one half-sweep
+  const double resid = 4.0 + lanes * (F32 ? 4.4e-6 : 12e-6);
+  const double sym = 6.0 + sym_rounds<T>(s, c->cus).planes * (F32 ? 1.0 : 1.45);
+  const double half = 2.0 * (npre + npost) * (4.0 + lanes * (F32 ? 3.8e-6 : 8.0e-6)) + resid;
+  double split = (npre + npost) * sym + resid;
+  if constexpr (F32)  // the last pre-smoothing sweep takes the residual along
+    if (c->opt.restriction == GMG_RESTRICT_MEAN)
+      split = (npre + npost - 1) * sym + sym_rounds<T, true>(s, c->cus).planes * 1.42;
+  double row = 1e300;
+  if (sym_row_waves(s) <= 2)
+    row = (npre + npost) * (6.0 + sym_row_rounds<T>(s, c->cus).planes * (F32 ? 0.9 : 1.3)) + resid;
+  // (the half-sweeps were a little faster where they are within 5%)
+  if (std::min(split, row) > 0.95 * half) return FINE_HALF;
+  return row < split ? FINE_ROW : FINE_SPLIT;
 }
-template <typename T>
-bool fused_sweeps(gmg_ctx* c) {
-  return c->opt.nu_pre >= 1 && c->opt.nu_post >= 1 && sym_chosen<T>(c);
-}
+bool fused_sweeps(gmg_ctx* c) { return c->opt.nu_pre >= 1 && c->opt.nu_post >= 1 && c->fine_form != FINE_HALF; }
 
 // z = M (s * u) on the finest level with right side u scaled by *bscale
 // (null = 1); z in the V-cycle precision, colour-split when there are at
@@ -1336,7 +1405,7 @@ void vcycle_fine(gmg_ctx* c, const double* u, const double* bscale, T* z) {
     vcycle_fine_cheb<T>(c, u, bscale, z);
   else if (has_legs(c, 0))
     vcycle_fine_legs<T>(c, u, bscale, z, false);
-  else if (fused_sweeps<T>(c))
+  else if (fused_sweeps(c))
     vcycle_fine_sym<T>(c, u, bscale, z, false);
   else
     vcycle_fine_split<T>(c, u, bscale, z, false);
@@ -1365,7 +1434,7 @@ void fmg_fine(gmg_ctx* c, const double* u, const double* bscale, T* z) {
     vcycle_fine_legs<T>(c, u, bscale, z, true);
     return;
   }
-  const bool fused = fused_sweeps<T>(c);
+  const bool fused = fused_sweeps(c);
   T* X0 = fused ? sym_buffer<T>(c, z, 0) : z;
   {
     const Launch l = pair_launch(s.nx, s.ny, s.nz / 2, 8192, 4, 1);
@@ -1803,7 +1872,7 @@ void cheb_step(gmg_ctx* c, int l, double* hcol, double* vs) {
     T* E = wsp<T>(c, c->L.xs);
     T* Bs = wsp<T>(c, c->L.b0);
     // one symmetric sweep from zero: colours 0, 1, 0
-    if (sym_chosen<T>(c)) {
+    if (c->fine_form != FINE_HALF) {
       sym_split<T, true>(c, E, E, Bs, r, nullptr, a, 0);
     } else {
       gs_split<T, true>(c, E, Bs, r, nullptr, a, 0);
@@ -2264,6 +2333,7 @@ int init_ctx(gmg_ctx* c, int nx, int ny, int nz, double hx, double hy, double hz
     plan_legs<float>(c);
   else
     plan_legs<double>(c);
+  c->fine_form = c->mixed ? choose_fine_form<float>(c) : choose_fine_form<double>(c);
   const int m = opt->restart;
   c->R.assign((size_t)m * m, 0.0);
   c->cs.assign(m, 0.0);
