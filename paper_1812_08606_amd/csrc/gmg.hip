@@ -33,8 +33,10 @@ namespace {
 
 constexpr size_t ALIGN = 256;
 constexpr int MAX_RESTART = 32;
-// device scalars after the Krylov methods': the failed-pivot flag of the
+// device scalars after the Krylov methods': of a renewal, the coefficient's
+// minimum and its count of non-finite values, and the failed-pivot flag of the
 // coarsest level's inverse
+constexpr int MISC_RENEWAL = 28;
 constexpr int MISC_BAD_PIVOT = 30;
 constexpr double BREAKDOWN_TOL = 1e-14;
 constexpr int CHEB_ARNOLDI = 10;  // Arnoldi steps of the Chebyshev bound estimate
@@ -379,11 +381,17 @@ int read_back(gmg_ctx* c, const double* dev, int n) {
 // Hierarchy set-up (per coefficient).
 // ---------------------------------------------------------------------------
 
+template <typename T>
+FaceCoef<T> face_coef(gmg_ctx* c, int l) {
+  const LevelOffsets& o = c->L.lv[l];
+  return FaceCoef<T>{wsp<T>(c, o.wx), wsp<T>(c, o.wy), wsp<T>(c, o.wz), wsp<T>(c, o.tp)};
+}
+
 // Inverse of the coarsest level's matrix into cinv (V-cycle precision), on the
 // GPU at every size (gmg_coarse.hpp): assembly, the symmetric sweep in NB x NB
-// blocks on the float64 matrix, and the copy of both triangles.  Nothing of
-// it visits the host but the failed-pivot flag.
-int coarse_inverse(gmg_ctx* c) {
+// blocks on the float64 matrix, and the copy of both triangles.  A pivot that
+// fails sets the flag at misc[MISC_BAD_PIVOT].
+void coarse_inverse(gmg_ctx* c) {
   const Layout& L = c->L;
   const int nl = (int)L.shapes.size();
   const LevelShape& s = L.shapes.back();
@@ -412,76 +420,52 @@ int coarse_inverse(gmg_ctx* c) {
     GMG_LAUNCH(c, "coarse_inverse", k_sweep_finish<float>, fl, (const double*)A, n, wsp<float>(c, L.cinv));
   else
     GMG_LAUNCH(c, "coarse_inverse", k_sweep_finish<double>, fl, (const double*)A, n, wsp<double>(c, L.cinv));
-  if (read_back(c, bad, 1) != GMG_OK) return GMG_ERR_HIP;
-  return c->pinned[0] == 0.0 ? GMG_OK : GMG_ERR_NONFINITE;
 }
 
+// Hierarchy of the coefficient c->a, queued without a wait: its check (finite
+// and positive) and float32 copy in one pass, the faces of every level in both
+// precisions, the coarsest inverse; then one read-back decides.  (A refused
+// coefficient leaves no usable hierarchy; the next renewal rebuilds all of
+// it.)  Waiting for the check before anything else, and a conversion launch per
+// face array, took 168 us at 128^3 against 64, 1.35 ms at 512^3 against 0.90
+// (mixed).
 int build_hierarchy(gmg_ctx* c) {
   Layout& L = c->L;
   const int nl = (int)L.shapes.size();
-  // check the coefficient: finite and positive
+  double* part = wsp<double>(c, L.partials);
+  double* misc = scal_misc(c);
   {
-    const Launch fl = flat_launch(c->N);
-    const int nb = std::min<int>(fl.grid.x, MAX_RED_BLOCKS);
-    Launch l2 = fl;
-    l2.grid.x = nb;
-    double* part = wsp<double>(c, L.partials);
-    GMG_LAUNCH(c, "check_coef", k_check_coef, l2, c->a, c->N, part);
-    std::vector<double> h(2 * (size_t)nb);
-    note(c, hipMemcpyAsync(h.data(), part, h.size() * 8, hipMemcpyDeviceToHost, c->stream));
-    note(c, hipStreamSynchronize(c->stream));
-    if (c->err != hipSuccess) return GMG_ERR_HIP;
-    double mn = 1e308, bad = 0;
-    for (int b = 0; b < nb; ++b) {
-      mn = std::min(mn, h[2 * b]);
-      bad += h[2 * b + 1];
-    }
-    if (bad > 0) return GMG_ERR_NONFINITE;
-    if (!(mn > 0.0)) return GMG_ERR_ARG;
-  }
-  if (c->mixed) {
-    const Launch fl = flat_launch(c->N);
-    GMG_LAUNCH(c, "convert_f64_f32", (k_convert<float, double>), fl, c->a, wsp<float>(c, L.a32), c->N);
+    Launch fl = flat_launch(c->N);
+    fl.grid.x = std::min<unsigned>(fl.grid.x, 8u * (unsigned)c->cus);
+    GMG_LAUNCH(c, "check_coef", k_check_coef, fl, c->a, c->N, c->mixed ? wsp<float>(c, L.a32) : (float*)nullptr, part);
+    const Launch one{dim3(1), dim3(FIN_THREADS, 1, 1), 0};
+    GMG_LAUNCH(c, "check_reduce", k_check_reduce, one, (const double*)part, fl.nblocks(), misc + MISC_RENEWAL);
   }
   for (int l = 1; l < nl; ++l) {
     const LevelShape& f = L.shapes[l - 1];
     const LevelShape& s = L.shapes[l];
     const LevelOffsets& o = L.lv[l];
+    FaceOut out{wsp<double>(c, o.wx64), wsp<double>(c, o.wy64), wsp<double>(c, o.wz64), wsp<double>(c, o.tp64), {}};
+    if (c->mixed) out.f = face_coef<float>(c, l);
     const Launch lc = col_launch(s.nx, s.ny, s.nz, 1 << 16);
     if (l == 1) {
-      GMG_LAUNCH(c, "faces_from_cells", k_faces_from_cells, lc, c->a, f.geom(), wsp<double>(c, o.wx64),
-                 wsp<double>(c, o.wy64), wsp<double>(c, o.wz64), wsp<double>(c, o.tp64), lc.kc);
+      GMG_LAUNCH(c, "faces_from_cells", k_faces_from_cells, lc, c->a, f.geom(), out, lc.kc);
     } else {
       const LevelOffsets& p = L.lv[l - 1];
       GMG_LAUNCH(c, "coarsen_faces", k_coarsen_faces, lc, wsp<double>(c, p.wx64), wsp<double>(c, p.wy64),
-                 wsp<double>(c, p.wz64), wsp<double>(c, p.tp64), f.geom(), wsp<double>(c, o.wx64),
-                 wsp<double>(c, o.wy64), wsp<double>(c, o.wz64), wsp<double>(c, o.tp64), lc.kc);
-    }
-    if (c->mixed) {
-      const size_t n = s.n(), nxy = (size_t)s.nx * s.ny;
-      const Launch fl = flat_launch(n);
-      GMG_LAUNCH(c, "convert_f64_f32", (k_convert<float, double>), fl, wsp<double>(c, o.wx64),
-                 wsp<float>(c, o.wx), n);
-      GMG_LAUNCH(c, "convert_f64_f32", (k_convert<float, double>), fl, wsp<double>(c, o.wy64),
-                 wsp<float>(c, o.wy), n);
-      GMG_LAUNCH(c, "convert_f64_f32", (k_convert<float, double>), fl, wsp<double>(c, o.wz64),
-                 wsp<float>(c, o.wz), n);
-      GMG_LAUNCH(c, "convert_f64_f32", (k_convert<float, double>), flat_launch(nxy), wsp<double>(c, o.tp64),
-                 wsp<float>(c, o.tp), nxy);
+                 wsp<double>(c, p.wz64), wsp<double>(c, p.tp64), f.geom(), out, lc.kc);
     }
   }
-  return coarse_inverse(c);
+  coarse_inverse(c);
+  if (read_back(c, misc + MISC_RENEWAL, 3) != GMG_OK) return GMG_ERR_HIP;
+  if (c->pinned[1] > 0) return GMG_ERR_NONFINITE;
+  if (!(c->pinned[0] > 0.0)) return GMG_ERR_ARG;
+  return c->pinned[2] == 0.0 ? GMG_OK : GMG_ERR_NONFINITE;
 }
 
 // ---------------------------------------------------------------------------
 // V-cycle (Sec. 3.2): zero initial guess, red-black symmetric Gauss-Seidel.
 // ---------------------------------------------------------------------------
-
-template <typename T>
-FaceCoef<T> face_coef(gmg_ctx* c, int l) {
-  const LevelOffsets& o = c->L.lv[l];
-  return FaceCoef<T>{wsp<T>(c, o.wx), wsp<T>(c, o.wy), wsp<T>(c, o.wz), wsp<T>(c, o.tp)};
-}
 
 // Profile name of a kernel: base + level ("fine" for level 0, "L<l>" for a
 // coarser one, "coarsest") + precision (the returned string lives as long as

@@ -112,7 +112,8 @@ __device__ __forceinline__ void sweep_pivot_block(double* S, double* Wb, double*
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int lr = lane & 15, lk = lane >> 4;
   bool fail = false;
-  for (int q = 0; q < NB / QB; ++q) {
+  const int nq = (min(NB, n - bk * NB) + QB - 1) / QB;  // (columns past the matrix are those of the identity)
+  for (int q = 0; q < nq; ++q) {
     if (wave == 0) {
       double m[QB];
 #pragma unroll
@@ -336,7 +337,9 @@ __global__ __launch_bounds__(256) void k_dense_assemble(FaceCoef<double> co, con
 // Coarsest level: x = A_L^{-1} b with the precomputed symmetric inverse, one
 // wave per row (a thread per row, as this kernel had before, put 3375 rows on
 // 14 of 256 CUs and waited for each element: 632 us at 2145 rows, float32).
-// The lanes stride the row in fixed order, then a wave reduction.
+// The lanes stride the row in fixed order, then a wave reduction; summed in
+// float64 (in float32 the sum's rounding left the first step's residual at
+// 4080 rows four times as large; 17 -> 25 us).
 template <typename T>
 __global__ __launch_bounds__(NTHREADS) void k_coarse_solve(const T* __restrict__ Ainv, const T* __restrict__ b,
                                                            T* __restrict__ x, int n) {
@@ -344,7 +347,7 @@ __global__ __launch_bounds__(NTHREADS) void k_coarse_solve(const T* __restrict__
   if (r >= n) return;
   const T* __restrict__ row = Ainv + (size_t)r * n;
   constexpr int U = 8;  // elements a lane loads per wait
-  T acc = T(0);
+  double acc = 0.0;
   for (int c0 = lane; c0 < n; c0 += 64 * U) {
     T v[U], w[U];
 #pragma unroll
@@ -354,11 +357,11 @@ __global__ __launch_bounds__(NTHREADS) void k_coarse_solve(const T* __restrict__
       w[u] = c < n ? b[cc] : T(0);
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) acc += v[u] * w[u];
+    for (int u = 0; u < U; ++u) acc += (double)v[u] * (double)w[u];
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
-  if (lane == 0) x[r] = acc;
+  if (lane == 0) x[r] = (T)acc;
 }
 
 }  // namespace gmg
