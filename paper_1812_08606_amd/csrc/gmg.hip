@@ -5,6 +5,8 @@
 
 #include <algorithm>
 #include <array>
+#include <atomic>
+#include <chrono>
 #include <cstdint>
 #include <cmath>
 #include <cstdio>
@@ -33,6 +35,9 @@ namespace {
 
 constexpr size_t ALIGN = 256;
 constexpr int MAX_RESTART = 32;
+// host buffer of a context: scalars read back, and last the flag of the
+// finalize launch that wrote them (k_finalize)
+constexpr int HOST_DOUBLES = MAX_RESTART + 9;
 // device scalars after the Krylov methods': of a renewal, the coefficient's
 // minimum and its count of non-finite values, and the failed-pivot flag of the
 // coarsest level's inverse
@@ -317,6 +322,7 @@ struct gmg_ctx {
   hipStream_t cap_stream = nullptr;  // capture only (the caller's may be the null stream)
   double* pinned;
   bool mapped;  // pinned is memory the GPU can write (not in fgmres_solve_static)
+  unsigned long long seq;  // finalize launches that wrote there
   hipError_t err;
   Profiler prof;
   // host Givens state
@@ -1536,18 +1542,36 @@ Launch red_launch(gmg_ctx* c) { return march_launch(c, c->nx); }
 // the same with one lane per x-pair of the finest level (nx even)
 Launch pair_red_launch(gmg_ctx* c) { return march_launch(c, c->nx / 2); }
 
+unsigned long long* host_flag(gmg_ctx* c) {
+  return reinterpret_cast<unsigned long long*>(c->pinned + HOST_DOUBLES - 1);
+}
+
 // host_at >= 0: the results also to c->pinned[host_at ..] where the GPU can
 // write there (fetch then needs no copy: a 2 to 4 us launch less per wait).
 void finalize(gmg_ctx* c, int nblocks, int nv, int mode, double* out, const double* scale, double* out2,
               int host_at = -1) {
   const Launch one{dim3(1), dim3(FIN_THREADS, 1, 1), 0};
   GMG_LAUNCH(c, "finalize", k_finalize, one, wsp<const double>(c, c->L.partials), nblocks, nv, mode, out, scale,
-             out2, host_at >= 0 && c->mapped ? c->pinned + host_at : (double*)nullptr);
+             out2, host_at >= 0 && c->mapped ? c->pinned + host_at : (double*)nullptr, host_flag(c),
+             host_at >= 0 ? ++c->seq : c->seq);
 }
 
-// Waits for n values at dev, which finalize also sent to c->pinned[0 ..].
+// Waits for n values at dev, which finalize also sent to c->pinned[0 ..]: for
+// the flag that the last of them set, FETCH_SPIN_US at most, then for the
+// stream.  (Launch, small kernel and stream wait take 11.0 us, launch, kernel
+// and flag 6.4: on small grids one of these per Arnoldi step.)
+constexpr int FETCH_SPIN_US = 400;
 int fetch(gmg_ctx* c, const double* dev, int n) {
   if (!c->mapped) return read_back(c, dev, n);
+  if (c->err == hipSuccess) {
+    const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(FETCH_SPIN_US);
+    do {
+      for (int i = 0; i < 64; ++i) {
+        if (__atomic_load_n(host_flag(c), __ATOMIC_ACQUIRE) == c->seq) return GMG_OK;
+        __builtin_ia32_pause();
+      }
+    } while (std::chrono::steady_clock::now() < until);
+  }
   note(c, hipStreamSynchronize(c->stream));
   return c->err == hipSuccess ? GMG_OK : GMG_ERR_HIP;
 }
@@ -2278,9 +2302,49 @@ size_t gmg_workspace_bytes(int nx, int ny, int nz, const gmg_options* opt) {
 
 namespace {
 
+// Pinned host buffers of destroyed contexts, kept for the next ones (328 bytes
+// each, at most HOST_BUFFERS_KEPT; the rest go back to the system):
+// allocating and freeing one took most of the 75 us that creating and
+// destroying a context adds to its renewal.  Portable across devices.  Every
+// entry point has waited for its launches when it returns, so nothing writes
+// to a buffer that is given back.
+constexpr size_t HOST_BUFFERS_KEPT = 16;
+std::atomic<unsigned long long> g_contexts{0};
+std::mutex g_host_mu;
+std::vector<double*> g_host_free;
+
+double* host_buffer_take() {
+  {
+    std::lock_guard<std::mutex> g(g_host_mu);
+    if (!g_host_free.empty()) {
+      double* p = g_host_free.back();
+      g_host_free.pop_back();
+      return p;
+    }
+  }
+  double* p = nullptr;
+  if (hipHostMalloc((void**)&p, HOST_DOUBLES * 8, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  return p;
+}
+
+void host_buffer_give(double* p) {
+  {
+    std::lock_guard<std::mutex> g(g_host_mu);
+    if (g_host_free.size() < HOST_BUFFERS_KEPT) {
+      if (g_host_free.capacity() == 0) g_host_free.reserve(HOST_BUFFERS_KEPT);
+      g_host_free.push_back(p);
+      return;
+    }
+  }
+  (void)hipHostFree(p);
+}
+
 // Context c (constructed by the caller) for the grid, coefficient and
 // layout L, on the workspace ws (checked by the caller) and the host buffer
-// host_buf of MAX_RESTART + 8 doubles for read-backs; builds the hierarchy.
+// host_buf of HOST_DOUBLES doubles for read-backs; builds the hierarchy.
 int init_ctx(gmg_ctx* c, int nx, int ny, int nz, double hx, double hy, double hz, const double* a_dev,
              const gmg_options* opt, void* ws, size_t ws_bytes, void* hip_stream, const Layout& L,
              double* host_buf, bool mapped) {
@@ -2306,6 +2370,8 @@ int init_ctx(gmg_ctx* c, int nx, int ny, int nz, double hx, double hy, double hz
   c->err = hipSuccess;
   c->pinned = host_buf;
   c->mapped = mapped;
+  c->seq = ++g_contexts << 32;  // (no two contexts share a value: buffers are reused)
+  *host_flag(c) = 0;
   {
     int dev = 0, n = 0;
     c->cus = hipGetDevice(&dev) == hipSuccess &&
@@ -2353,8 +2419,8 @@ int gmg_setup(int nx, int ny, int nz, double hx, double hy, double hz, const dou
     return GMG_ERR_WORKSPACE;
   gmg_ctx* c = new (std::nothrow) gmg_ctx();
   if (!c) return GMG_ERR_ARG;
-  double* pinned = nullptr;
-  if (hipHostMalloc((void**)&pinned, (size_t)(MAX_RESTART + 8) * 8, hipHostMallocDefault) != hipSuccess) {
+  double* pinned = host_buffer_take();
+  if (!pinned) {
     delete c;
     return GMG_ERR_HIP;
   }
@@ -2596,7 +2662,7 @@ int fgmres_solve_static(int nx, int ny, int nz, double hx, double hy, double hz,
   if (!ws) return GMG_ERR_HIP;
   // one call at a time per GPU: every call on it uses the same array
   std::lock_guard<std::mutex> g(g_scratch_mu[dev]);
-  double host_buf[MAX_RESTART + 8];
+  double host_buf[HOST_DOUBLES];
   gmg_ctx c;
   st = init_ctx(&c, nx, ny, nz, hx, hy, hz, a_dev, opt, ws, GMG_STATIC_SCRATCH_BYTES, hip_stream, L, host_buf,
                 false);
@@ -2885,7 +2951,7 @@ void gmg_destroy(gmg_ctx* c) {
   for (hipEvent_t e : c->prof.pool) (void)hipEventDestroy(e);
   drop_graphs(c);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
-  if (c->pinned) (void)hipHostFree(c->pinned);
+  if (c->pinned) host_buffer_give(c->pinned);
   delete c;
 }
 

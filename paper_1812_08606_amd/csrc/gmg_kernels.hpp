@@ -765,7 +765,8 @@ __global__ __launch_bounds__(NTHREADS) void k_update(double* __restrict__ phi, s
 //              sum is 0)
 //   FIN_RESID  (nv = 2) out[0], out[1] the sums, out[2] = sqrt of the second,
 //              out2[0] its inverse (0 if it is 0)
-// The results also go to host (pinned host memory) when it is given.
+// The results also go to host (pinned host memory) when it is given, and then
+// seq to *flag, with a system-scope release: the host waits for that value.
 enum { FIN_SUM = 0, FIN_DOTS = 1, FIN_NORM = 2, FIN_RESID = 3 };
 constexpr int FIN_THREADS = 1024;
 constexpr int FIN_BATCH = 8;  // partials of one vector a thread loads per wait
@@ -773,7 +774,8 @@ constexpr int FIN_BATCH = 8;  // partials of one vector a thread loads per wait
 __global__ __launch_bounds__(FIN_THREADS) void k_finalize(const double* __restrict__ partials, int nblocks, int nv,
                                                           int mode, double* __restrict__ out,
                                                           const double* __restrict__ scale,
-                                                          double* __restrict__ out2, double* __restrict__ host) {
+                                                          double* __restrict__ out2, double* __restrict__ host,
+                                                          unsigned long long* flag, unsigned long long seq) {
   __shared__ double sm[MAXV][FIN_THREADS / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // every vector at once: its share of the 16 waves (a power of two) strides
@@ -814,6 +816,13 @@ __global__ __launch_bounds__(FIN_THREADS) void k_finalize(const double* __restri
       out[2] = n;
       if (host) host[2] = n;
       out2[0] = n > 0.0 ? 1.0 / n : 0.0;
+    }
+  }
+  if (host) {
+    __syncthreads();
+    if (tid == 0) {
+      __threadfence_system();
+      __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
   }
 }

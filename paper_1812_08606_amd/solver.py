@@ -42,6 +42,9 @@ class SolveResult:
 
 
 def _check_field(t: torch.Tensor, shape, name: str, device=None):
+    if (type(t) is torch.Tensor and t.dtype is torch.float64 and t.shape == shape and t.device == device
+            and t.is_contiguous() and t.is_cuda):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch tensor")
     if t.dtype != torch.float64:
@@ -58,6 +61,13 @@ def _check_field(t: torch.Tensor, shape, name: str, device=None):
 
 def _ptr(t: torch.Tensor):
     return ctypes.c_void_p(t.data_ptr())
+
+
+# The raw stream handle without building a Stream object (2 us per call)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+if _raw_stream is None:
+    def _raw_stream(index):
+        return torch.cuda.current_stream(index).cuda_stream
 
 
 class GMGPoisson:
@@ -158,10 +168,20 @@ class GMGPoisson:
 
     # -- plumbing ---------------------------------------------------------
     def _sync_stream(self):
-        s = torch.cuda.current_stream(self.device).cuda_stream
+        s = _raw_stream(self.device.index)
         if s != self._stream:
             self._lib.gmg_set_stream(self._ctx, ctypes.c_void_p(s))
             self._stream = s
+
+    def _call(self, entry, *args):
+        """The C entry on this handle's device, its launches on the caller's
+        current stream there."""
+        if torch.cuda.current_device() == self.device.index:
+            self._sync_stream()
+            return entry(self._ctx, *args)
+        with torch.cuda.device(self.device):
+            self._sync_stream()
+            return entry(self._ctx, *args)
 
     def __del__(self):
         ctx = getattr(self, "_ctx", None)
@@ -191,9 +211,7 @@ class GMGPoisson:
     # -- operations -------------------------------------------------------
     def update_coefficient(self, a: torch.Tensor):
         _check_field(a, self.shape, "a", self.device)
-        with torch.cuda.device(self.device):
-            self._sync_stream()
-            st = self._lib.gmg_update_coefficient(self._ctx, _ptr(a))
+        st = self._call(self._lib.gmg_update_coefficient, _ptr(a))
         if st != OK:
             raise GMGError(st, "gmg_update_coefficient")
         self._a = a
@@ -215,9 +233,7 @@ class GMGPoisson:
         hist = (ctypes.c_double * cap)()
         its, nh = ctypes.c_int(0), ctypes.c_int(0)
         rel = ctypes.c_double(float("nan"))
-        with torch.cuda.device(self.device):
-            self._sync_stream()
-            st = self._lib.fgmres_solve(self._ctx, _ptr(f), float(phi_bot), float(phi_top), float(tol),
+        st = self._call(self._lib.fgmres_solve, _ptr(f), float(phi_bot), float(phi_top), float(tol),
                                         _ptr(out), use_x0, ctypes.byref(its), hist, cap,
                                         ctypes.byref(nh), ctypes.byref(rel))
         if st < 0 and raise_on_error:
@@ -229,9 +245,7 @@ class GMGPoisson:
         """A x - lifting (left side of e18 with the given plate values)."""
         _check_field(x, self.shape, "x", self.device)
         y = torch.empty_like(x)
-        with torch.cuda.device(self.device):
-            self._sync_stream()
-            st = self._lib.gmg_apply_operator(self._ctx, _ptr(x), _ptr(y), float(phi_bot), float(phi_top))
+        st = self._call(self._lib.gmg_apply_operator, _ptr(x), _ptr(y), float(phi_bot), float(phi_top))
         if st != OK:
             raise GMGError(st, "gmg_apply_operator")
         return y
@@ -247,9 +261,7 @@ class GMGPoisson:
     def _cycle(self, v: torch.Tensor, entry: str) -> torch.Tensor:
         _check_field(v, self.shape, "v", self.device)
         z = torch.empty_like(v)
-        with torch.cuda.device(self.device):
-            self._sync_stream()
-            st = getattr(self._lib, entry)(self._ctx, _ptr(v), _ptr(z))
+        st = self._call(getattr(self._lib, entry), _ptr(v), _ptr(z))
         if st != OK:
             raise GMGError(st, entry)
         return z
@@ -273,9 +285,7 @@ class GMGPoisson:
             if x0.data_ptr() != phi.data_ptr():
                 phi.copy_(x0)
         its, napp, rel = ctypes.c_int(), ctypes.c_int(), ctypes.c_double()
-        with torch.cuda.device(self.device):
-            self._sync_stream()
-            st = self._lib.gmg_krylov_solve(self._ctx, self.KRYLOV[method], _ptr(f), float(phi_bot),
+        st = self._call(self._lib.gmg_krylov_solve, self.KRYLOV[method], _ptr(f), float(phi_bot),
                                             float(phi_top), float(tol), _ptr(phi), int(x0 is not None),
                                             ctypes.byref(its), ctypes.byref(napp), ctypes.byref(rel))
         if st < 0 and raise_on_error:
@@ -294,9 +304,7 @@ class GMGPoisson:
         _check_field(f, self.shape, "f", self.device)
         prm = _lib.StepParams(float(eps0_over_e), float(tau_eff), float(mu_e), float(mu_p),
                               (ctypes.c_double * 3)(*[float(v) for v in De]))
-        with torch.cuda.device(self.device):
-            self._sync_stream()
-            st = self._lib.gmg_assemble_elliptic(self._ctx, _ptr(n_e), _ptr(n_p), ctypes.byref(prm), _ptr(a),
+        st = self._call(self._lib.gmg_assemble_elliptic, _ptr(n_e), _ptr(n_p), ctypes.byref(prm), _ptr(a),
                                                  _ptr(f))
         if st != OK:
             raise GMGError(st, "gmg_assemble_elliptic")
@@ -308,9 +316,7 @@ class GMGPoisson:
         outs = out if out is not None else tuple(torch.empty_like(phi) for _ in range(4))
         for o, nm in zip(outs, ("E_x", "E_y", "E_z", "|E|")):
             _check_field(o, self.shape, nm, self.device)
-        with torch.cuda.device(self.device):
-            self._sync_stream()
-            st = self._lib.gmg_electric_field(self._ctx, _ptr(phi), float(phi_bot), float(phi_top),
+        st = self._call(self._lib.gmg_electric_field, _ptr(phi), float(phi_bot), float(phi_top),
                                               *[_ptr(o) for o in outs])
         if st != OK:
             raise GMGError(st, "gmg_electric_field")
@@ -324,9 +330,7 @@ class GMGPoisson:
         _check_field(phi, self.shape, "phi", self.device)
         _check_field(lam, self.shape, "lam", self.device)
         _check_field(out, self.shape, "out", self.device)
-        with torch.cuda.device(self.device):
-            self._sync_stream()
-            st = self._lib.gmg_face_flux_grad(self._ctx, _ptr(phi), _ptr(lam), float(phi_bot),
+        st = self._call(self._lib.gmg_face_flux_grad, _ptr(phi), _ptr(lam), float(phi_bot),
                                               float(phi_top), _ptr(out))
         if st != OK:
             raise GMGError(st, "gmg_face_flux_grad")
@@ -405,9 +409,7 @@ class SemiImplicitStepper:
         for t, nm in ((n_e, "n_e"), (n_p, "n_p"), (l_e, "L_e"), (l_p, "L_p"), (out_e, "out n_e"),
                       (out_p, "out n_p")):
             _check_field(t, self.shape, nm, self.device)
-        with torch.cuda.device(self.device):
-            self.solver._sync_stream()
-            st = self._lib.gmg_density_update(self.solver._ctx, _ptr(n_e), _ptr(n_p), _ptr(l_e), _ptr(l_p),
+        st = self.solver._call(self._lib.gmg_density_update, _ptr(n_e), _ptr(n_p), _ptr(l_e), _ptr(l_p),
                                               float(dt), _ptr(out_e), _ptr(out_p))
         if st != OK:
             raise GMGError(st, "gmg_density_update")
@@ -424,9 +426,7 @@ class SemiImplicitStepper:
         prm = _lib.StepParams(eps, float(tau_eff), mu_e, mu_p, (ctypes.c_double * 3)(*De))
         its = ctypes.c_int(0)
         rel = ctypes.c_double(float("nan"))
-        with torch.cuda.device(self.device):
-            self.solver._sync_stream()
-            st = self._lib.gmg_elliptic_step(self.solver._ctx, _ptr(n_e), _ptr(n_p), ctypes.byref(prm), *self.bc,
+        st = self.solver._call(self._lib.gmg_elliptic_step, _ptr(n_e), _ptr(n_p), ctypes.byref(prm), *self.bc,
                                              self.tol, _ptr(self.a), _ptr(self.f), _ptr(self.phi),
                                              int(self._warm), *[_ptr(e) for e in self.E], ctypes.byref(its),
                                              ctypes.byref(rel))
