@@ -21,12 +21,12 @@ namespace gmg {
 // inverts the next pivot block, so its serial chain of NB pivots runs beside
 // the other tiles.  A zero, negative or non-finite pivot sets *bad (read back
 // once, after the last step).
-// Measured (renewal of the whole hierarchy): 4080 cells 187-289 -> 3.7 ms,
-// 1287 cells 12.6 -> 1.05 ms, 343 cells 2.7 -> 0.4 ms against Gauss-Jordan
+// Measured (renewal of the whole hierarchy): 4080 cells 187-289 -> 3.5 ms,
+// 1287 cells 12.6 -> 0.95 ms, 343 cells 2.7 -> 0.35 ms against Gauss-Jordan
 // elimination with two launches per cell (above 1024 cells) and a host
-// Cholesky inverse (below).  A step takes about 55 us at 4080 cells, the
-// update (43 us) bound by reading and writing the half matrix, and 30-45 us
-// below 2000 cells, where the chain of pivots and the two launches bound it.
+// Cholesky inverse (below).  A step takes about 51 us at 4080 cells, the
+// update (40 us) bound by reading and writing the half matrix, and 30-42 us
+// below 2200 cells, where the chain of pivots and the two launches bound it.
 constexpr int NB = 64;
 // rows of a tile in LDS are 66 doubles apart: the 16 rows x 2 columns that 32
 // lanes read for a 16 x 16 x 4 matrix instruction fall on 64 different banks
@@ -36,16 +36,17 @@ constexpr int INV_THREADS = 256;
 typedef double d4 __attribute__((ext_vector_type(4)));
 
 // acc (rows 32 wr .., columns 32 wc .. of a 64 x 64 product, four 16 x 16
-// pieces) += X Y^T with X and Y in LDS as [row][k], LDT apart.  Operand lanes
-// of v_mfma_f64_16x16x4: row or column l % 16, k = l / 16; result register i:
-// row 4 i + l / 16, column l % 16.
+// pieces) += X Y^T with X and Y in LDS as [row][k], K columns, rows LD apart.
+// Operand lanes of v_mfma_f64_16x16x4: row or column l % 16, k = l / 16; result
+// register i: row 4 i + l / 16, column l % 16.
+template <int K, int LD>
 __device__ __forceinline__ void tile_mul(d4 (&acc)[2][2], const double* X, const double* Y, int wr, int wc) {
   const int l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
-  const double* xr = X + (32 * wr + lr) * LDT + lk;
-  const double* yr = Y + (32 * wc + lr) * LDT + lk;
+  const double* xr = X + (32 * wr + lr) * LD + lk;
+  const double* yr = Y + (32 * wc + lr) * LD + lk;
 #pragma unroll 4
-  for (int k = 0; k < NB; k += 4) {
-    const double x0 = xr[k], x1 = xr[16 * LDT + k], y0 = yr[k], y1 = yr[16 * LDT + k];
+  for (int k = 0; k < K; k += 4) {
+    const double x0 = xr[k], x1 = xr[16 * LD + k], y0 = yr[k], y1 = yr[16 * LD + k];
     acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, y0, acc[0][0], 0, 0, 0);
     acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, y1, acc[0][1], 0, 0, 0);
     acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, y0, acc[1][0], 0, 0, 0);
@@ -96,14 +97,28 @@ __device__ __forceinline__ double readlane(double v, int lane) {
   return __builtin_bit_cast(double, int2{__builtin_amdgcn_readlane(w.x, lane), __builtin_amdgcn_readlane(w.y, lane)});
 }
 
+// 1 / d to about an ulp: the hardware estimate (2^-24) and two Newton steps (a
+// division is a chain more than twice as long, and every pivot waits for
+// one).  Outside the range where these are finite the division itself.
+__device__ __forceinline__ double rcp_f64(double d) {
+  double y = __builtin_amdgcn_rcp(d);
+  y = __builtin_fma(__builtin_fma(-d, y, 1.0), y, y);
+  y = __builtin_fma(__builtin_fma(-d, y, 1.0), y, y);
+  return isfinite(y) ? y : 1.0 / d;
+}
+
 // Sweeps the whole NB x NB block in S (symmetric, positive definite; LDS,
 // [row][column]) and stores the result, -S^{-1}, in the diagonal tile bk of
 // A.  QB columns at a time: one wave sweeps their QB pivots on the 64 x QB
 // panel, a row per lane in registers, the pivot row by readlane (no barrier
 // inside the chain), which leaves W = C P; then all four waves apply the
 // rank-QB update S_ij -= W_i C_j^T to the other 16 x 16 pieces with matrix
-// instructions.   (One barrier and one division per
-// pivot over the whole block took 50 us; this takes about 12.)
+// instructions.  A swept row is not scaled by its pivot's reciprocal at once:
+// the lane keeps the factor to the end of the panel (its later updates, m -=
+// (m_p / d) row, are the same with and without it), so a pivot costs one
+// multiplication per column.  (One barrier and one division per pivot over the
+// whole block took 50 us, scaling each row at once and a division 12; this
+// takes about 10.)
 constexpr int QB = 16;
 constexpr int LDW = QB + 2;
 
@@ -115,30 +130,25 @@ __device__ __forceinline__ void sweep_pivot_block(double* S, double* Wb, double*
   const int nq = (min(NB, n - bk * NB) + QB - 1) / QB;  // (columns past the matrix are those of the identity)
   for (int q = 0; q < nq; ++q) {
     if (wave == 0) {
-      double m[QB];
+      double m[QB], s = 1.0;
 #pragma unroll
       for (int c = 0; c < QB; ++c) m[c] = S[lane * LDT + QB * q + c];
 #pragma unroll
       for (int p = 0; p < QB; ++p) {
         const int pr = QB * q + p;
-        double row[QB];
-#pragma unroll
-        for (int c = 0; c < QB; ++c) row[c] = readlane(m[c], pr);
-        const double d = row[p];
+        const double d = readlane(m[p], pr);
         fail |= !(d > 0.0) || !isfinite(d);
-        const double id = 1.0 / d;
-        const double f = m[p] * id;
+        const double id = rcp_f64(d);
         const bool own = lane == pr;
+        const double f = own ? 0.0 : m[p] * id;
 #pragma unroll
-        for (int c = 0; c < QB; ++c) {
-          if (c == p)
-            m[c] = own ? -id : f;
-          else
-            m[c] = own ? row[c] * id : m[c] - f * row[c];
-        }
+        for (int c = 0; c < QB; ++c)
+          if (c != p) m[c] = __builtin_fma(-f, readlane(m[c], pr), m[c]);
+        m[p] = own ? -1.0 : f;
+        s = own ? id : s;
       }
 #pragma unroll
-      for (int c = 0; c < QB; ++c) Wb[lane * LDW + c] = m[c];
+      for (int c = 0; c < QB; ++c) Wb[lane * LDW + c] = m[c] * s;
     }
     __syncthreads();
     constexpr int NP = NB / QB - 1;  // 16 x 16 pieces per side outside the swept ones
@@ -197,7 +207,7 @@ __global__ __launch_bounds__(INV_THREADS) void k_sweep_panel(double* __restrict_
   }
   const int w = threadIdx.x >> 6, wr = w >> 1, wc = w & 1;
   d4 acc[2][2] = {};
-  tile_mul(acc, X, P, wr, wc);  // C_i (-P)^T = -W_i
+  tile_mul<NB, LDT>(acc, X, P, wr, wc);  // C_i (-P)^T = -W_i
   tile_each(acc, wr, wc, [&](int r, int c, double v) {
     const int gi = i * NB + r, gk = k * NB + c;
     if (gi < n && gk < n) A[i > k ? (size_t)gi * n + gk : (size_t)gk * n + gi] = -v;
@@ -206,16 +216,27 @@ __global__ __launch_bounds__(INV_THREADS) void k_sweep_panel(double* __restrict_
 
 // A_ij -= W_i C_j^T on every tile i >= j outside block row and column k; the
 // tile (k+1, k+1), first in the grid, is then swept as the next pivot block.
+// The operands pass through LDS KH columns at a time, the second half's loads
+// in flight under the first half's products: 45 KB per block instead of 79, so
+// three blocks share a CU and cover each other's loads (43 -> 40 us at 4080
+// cells; 128-wide steps with 128 x 128 blocks, half the traffic, took 86 us per
+// step, bound by the two pivot tiles one after the other).
+constexpr int KH = NB / 2;
+constexpr int LDH = KH + 2;  // (as LDT: 16 rows x 2 columns on 64 banks)
+
 __global__ __launch_bounds__(INV_THREADS) void k_sweep_update(double* __restrict__ A, int n, int nb, int k,
                                                               const double* __restrict__ C,
                                                               double* __restrict__ bad) {
-  __shared__ double X[NB * LDT], Y[NB * LDT];
+  __shared__ double buf[2 * NB * LDH];  // X and Y halves; then the pivot block
   __shared__ double Wb[NB * LDW];
+  static_assert(2 * NB * LDH >= NB * LDT, "the pivot block does not fit the operand buffer");
+  double *X = buf, *Y = buf + NB * LDH;
   const bool next = blockIdx.x == 0;
   int i, j;
   if (next) {
     i = j = k + 1;
     if (i >= nb) return;
+    __builtin_amdgcn_s_setprio(3);  // the chain of pivots goes before the tiles that share its CU
   } else {
     // tile number blockIdx.x - 1 in the order (0,0), (1,0), (1,1), (2,0), ...
     const int t = blockIdx.x - 1;
@@ -225,39 +246,55 @@ __global__ __launch_bounds__(INV_THREADS) void k_sweep_update(double* __restrict
     j = t - i * (i + 1) / 2;
     if (i == k || j == k || (i == j && i == k + 1)) return;
   }
-  const int w = threadIdx.x >> 6, wr = w >> 1, wc = w & 1;
-  // the tile itself first (clamped addresses), in flight while W_i and C_j
-  // go to LDS and are multiplied
-  d4 old[2][2] = {};
-  {
-    const int l = threadIdx.x & 63;
+  const int w = threadIdx.x >> 6, wr = w >> 1, wc = w & 1, l = threadIdx.x & 63;
+  // half h of W_i (block column k; stored transposed for i < k) and of C_j
+  constexpr int NL = NB * KH / INV_THREADS;
+  double xv[NL], yv[NL];
+  const bool tr = i < k;
+  auto load = [&](int h) {
 #pragma unroll
-    for (int p = 0; p < 2; ++p)
-#pragma unroll
-      for (int q = 0; q < 2; ++q)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int gi = min(i * NB + 32 * wr + 16 * p + 4 * e + (l >> 4), n - 1);
-          const int gj = min(j * NB + 32 * wc + 16 * q + (l & 15), n - 1);
-          old[p][q][e] = A[(size_t)gi * n + gj];
-        }
-  }
-  tile_load(X, A, n, i, k, 0.0);  // W_i
-  {
-    const int c = threadIdx.x % NB, rt = threadIdx.x / NB;
-    double v[TILE_LOADS];
-#pragma unroll
-    for (int u = 0; u < TILE_LOADS; ++u)
-      v[u] = C[(size_t)min(j * NB + rt + u * (INV_THREADS / NB), n - 1) * NB + c];
-#pragma unroll
-    for (int u = 0; u < TILE_LOADS; ++u) {
-      const int r = rt + u * (INV_THREADS / NB);
-      Y[r * LDT + c] = j * NB + r < n ? v[u] : 0.0;
+    for (int u = 0; u < NL; ++u) {
+      const int e = threadIdx.x + u * INV_THREADS;
+      // X: rows of W_i; along its columns when stored so, along its rows when transposed
+      const int r = tr ? e % NB : e / KH, c = KH * h + (tr ? e / NB : e % KH);
+      const int gi = min(i * NB + r, n - 1), gk = min(k * NB + c, n - 1);
+      xv[u] = A[tr ? (size_t)gk * n + gi : (size_t)gi * n + gk];
+      const int ry = e / KH, cy = KH * h + e % KH;
+      yv[u] = C[(size_t)min(j * NB + ry, n - 1) * NB + cy];
     }
-  }
-  __syncthreads();
+  };
+  auto store = [&](int h) {
+#pragma unroll
+    for (int u = 0; u < NL; ++u) {
+      const int e = threadIdx.x + u * INV_THREADS;
+      const int r = tr ? e % NB : e / KH, c = tr ? e / NB : e % KH;
+      X[r * LDH + c] = (i * NB + r < n && k * NB + KH * h + c < n) ? xv[u] : 0.0;
+      const int ry = e / KH;
+      Y[ry * LDH + e % KH] = j * NB + ry < n ? yv[u] : 0.0;
+    }
+  };
+  load(0);
+  // the tile itself (clamped addresses), in flight under the products
+  d4 old[2][2];
+#pragma unroll
+  for (int p = 0; p < 2; ++p)
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int gi = min(i * NB + 32 * wr + 16 * p + 4 * e + (l >> 4), n - 1);
+        const int gj = min(j * NB + 32 * wc + 16 * q + (l & 15), n - 1);
+        old[p][q][e] = A[(size_t)gi * n + gj];
+      }
   d4 acc[2][2] = {};
-  tile_mul(acc, X, Y, wr, wc);
+  store(0);
+  __syncthreads();
+  load(1);
+  tile_mul<KH, LDH>(acc, X, Y, wr, wc);
+  __syncthreads();
+  store(1);
+  __syncthreads();
+  tile_mul<KH, LDH>(acc, X, Y, wr, wc);
 #pragma unroll
   for (int p = 0; p < 2; ++p)
 #pragma unroll
@@ -269,13 +306,13 @@ __global__ __launch_bounds__(INV_THREADS) void k_sweep_update(double* __restrict
     });
     return;
   }
-  __syncthreads();  // every wave is done with X
+  __syncthreads();  // every wave is done with X and Y
   tile_each(acc, wr, wc, [&](int r, int c, double v) {
     const int gi = i * NB + r, gj = j * NB + c;
-    X[r * LDT + c] = (gi < n && gj < n) ? v : (r == c ? 1.0 : 0.0);
+    buf[r * LDT + c] = (gi < n && gj < n) ? v : (r == c ? 1.0 : 0.0);
   });
   __syncthreads();
-  sweep_pivot_block(X, Wb, A, n, i, bad);
+  sweep_pivot_block(buf, Wb, A, n, i, bad);
 }
 
 // The inverse, both triangles, in the V-cycle precision: out_ij = -A_ij for
