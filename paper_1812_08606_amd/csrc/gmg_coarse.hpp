@@ -97,13 +97,10 @@ __device__ __forceinline__ double readlane(double v, int lane) {
   return __builtin_bit_cast(double, int2{__builtin_amdgcn_readlane(w.x, lane), __builtin_amdgcn_readlane(w.y, lane)});
 }
 
-// 1 / d to about an ulp: the hardware estimate (2^-24) and two Newton steps (a
-// division is a chain more than twice as long, and every pivot waits for
-// one).  Outside the range where these are finite the division itself.
-__device__ __forceinline__ double rcp_f64(double d) {
-  double y = __builtin_amdgcn_rcp(d);
-  y = __builtin_fma(__builtin_fma(-d, y, 1.0), y, y);
-  y = __builtin_fma(__builtin_fma(-d, y, 1.0), y, y);
+// 1 / d of a pivot: recip, a chain less than half as long as the division's
+// (every pivot waits for one); the division itself where recip is not finite.
+__device__ __forceinline__ double rcp_pivot(double d) {
+  const double y = recip(d);
   return isfinite(y) ? y : 1.0 / d;
 }
 
@@ -138,7 +135,7 @@ __device__ __forceinline__ void sweep_pivot_block(double* S, double* Wb, double*
         const int pr = QB * q + p;
         const double d = readlane(m[p], pr);
         fail |= !(d > 0.0) || !isfinite(d);
-        const double id = rcp_f64(d);
+        const double id = rcp_pivot(d);
         const bool own = lane == pr;
         const double f = own ? 0.0 : m[p] * id;
 #pragma unroll
