@@ -89,6 +89,8 @@ struct Layout {
   std::vector<LevelShape> shapes;
   std::vector<LevelOffsets> lv;
   size_t V, Z, a32, b0, xs, partials, scal, cinv, total;
+  size_t pack;  // pairs of the levels of the one-workgroup bottom kernel
+  size_t maps;  // V-cycle and full multigrid maps of a 4 x 4 x 4 level above a coarsest 2 x 2 x 2 (0: none)
   size_t cmat;  // mixed: float64 matrix of the coarsest level while it is inverted (in float64, cinv itself)
   size_t cr0, cd0;  // Chebyshev smoother, finest level: float64 natural residual, T colour-split direction
   size_t rr;        // transpose restriction: residual of the level being restricted (finest: float64)
@@ -118,6 +120,42 @@ bool options_valid(const gmg_options* o) {
       (o->smoother != GMG_SMOOTH_RBGS || o->cold_cycle != GMG_CYCLE_V || o->warm_cycle != GMG_CYCLE_V))
     return false;
   return true;
+}
+
+// The levels small enough for the one-workgroup bottom kernel: the first
+// level l >= 1 from which every level has at most BOTTOM_MAX_CELLS cells, the
+// coarsest at most BOTTOM_MAX_COARSEST, and at most BOTTOM_MAX_LEVELS levels
+// remain; -1 when that leaves only the coarsest (a plain direct solve).
+constexpr size_t BOTTOM_MAX_CELLS = 4096;
+constexpr size_t BOTTOM_MAX_COARSEST = 512;
+constexpr size_t BOTTOM_MAX_SUM = 4704;  // >= 4096 (1 + 1/8 + 1/64 + ...)
+
+int bottom_level(const Layout& L) {
+  const int nl = (int)L.shapes.size();
+  if (nl < 3 || L.shapes.back().n() > BOTTOM_MAX_COARSEST) return -1;
+  int l = nl - 1;
+  size_t cells = L.shapes[l].n();
+  while (l > 1 && L.shapes[l - 1].n() <= BOTTOM_MAX_CELLS && nl - (l - 1) <= BOTTOM_MAX_LEVELS &&
+         cells + L.shapes[l - 1].n() <= BOTTOM_MAX_SUM) {
+    --l;
+    cells += L.shapes[l].n();
+  }
+  return l < nl - 1 ? l : -1;
+}
+
+// Whether the one-workgroup bottom kernel ends on a 4 x 4 x 4 level (at least
+// one more level between it and the finest).
+bool has_maps(const Layout& L) {
+  if (L.shapes.size() < 4) return false;
+  const LevelShape& s = L.shapes[L.shapes.size() - 2];
+  return s.nx == 4 && s.ny == 4 && s.nz == 4;
+}
+
+// x-pairs of the levels l0 .. l1 - 1.
+int pairs_of(const Layout& L, int l0, int l1) {
+  size_t n = 0;
+  for (int l = l0; l < l1; ++l) n += L.shapes[l].n() / 2;
+  return (int)n;
 }
 
 int make_layout(int nx, int ny, int nz, double hx, double hy, double hz, const gmg_options* o, Layout* L) {
@@ -193,6 +231,12 @@ int make_layout(int nx, int ny, int nz, double hx, double hy, double hz, const g
   L->scal = take((size_t)(L->m * (L->m + 2) + (L->m + 2) + 32) * 8);
   const size_t nc = last.n();
   L->cinv = take(nc * nc * L->tsize);
+  const int lb = cheb || o->restriction == GMG_RESTRICT_TRANSPOSE ? -1 : bottom_level(*L);
+  L->pack = lb < 0 ? 0 : take((size_t)pairs_of(*L, lb, nl - 1) * 16 *
+                              (mixed ? PackedPair<float>::chunks : PackedPair<double>::chunks));
+  L->maps = lb < 0 || !has_maps(*L)
+                ? 0
+                : take((size_t)2 * MAP_CELLS * L->tsize * (mixed ? MAP_LD<float> : MAP_LD<double>));
   // the Krylov basis is free during a renewal and holds the matrix unless the
   // grid has few levels
   L->cmat = !mixed ? 0 : nc * nc * 8 <= (size_t)nvslots * L->ldv * 8 ? L->V : take(nc * nc * 8);
@@ -200,27 +244,6 @@ int make_layout(int nx, int ny, int nz, double hx, double hy, double hz, const g
                 "the block column of the coarsest level's inverse does not fit the partials");
   L->total = off;
   return GMG_OK;
-}
-
-// The levels small enough for the one-workgroup bottom kernel: the first
-// level l >= 1 from which every level has at most BOTTOM_MAX_CELLS cells, the
-// coarsest at most BOTTOM_MAX_COARSEST, and at most BOTTOM_MAX_LEVELS levels
-// remain; -1 when that leaves only the coarsest (a plain direct solve).
-constexpr size_t BOTTOM_MAX_CELLS = 4096;
-constexpr size_t BOTTOM_MAX_COARSEST = 512;
-constexpr size_t BOTTOM_MAX_SUM = 4704;  // >= 4096 (1 + 1/8 + 1/64 + ...)
-
-int bottom_level(const Layout& L) {
-  const int nl = (int)L.shapes.size();
-  if (nl < 3 || L.shapes.back().n() > BOTTOM_MAX_COARSEST) return -1;
-  int l = nl - 1;
-  size_t cells = L.shapes[l].n();
-  while (l > 1 && L.shapes[l - 1].n() <= BOTTOM_MAX_CELLS && nl - (l - 1) <= BOTTOM_MAX_LEVELS &&
-         cells + L.shapes[l - 1].n() <= BOTTOM_MAX_SUM) {
-    --l;
-    cells += L.shapes[l].n();
-  }
-  return l < nl - 1 ? l : -1;
 }
 
 struct Launch {
@@ -428,6 +451,63 @@ void coarse_inverse(gmg_ctx* c) {
     GMG_LAUNCH(c, "coarse_inverse", k_sweep_finish<double>, fl, (const double*)A, n, wsp<double>(c, L.cinv));
 }
 
+// Arguments of the bottom kernel for the levels l0 to l1, the last of them
+// solved by the coarsest inverse or (a level above it) by its maps.
+template <typename T>
+BottomArgs<T> bottom_args(gmg_ctx* c, int l0, int l1) {
+  BottomArgs<T> A{};
+  A.nlev = l1 - l0 + 1;
+  A.w = wsp<const T>(c, c->L.pack);
+  A.npairs = pairs_of(c->L, c->bottom_from, (int)c->L.shapes.size() - 1);
+  int off = 0;
+  for (int q = 0; q < A.nlev; ++q) {
+    const LevelShape& s = c->L.shapes[l0 + q];
+    A.g[q] = s.geom();
+    if (q == A.nlev - 1) break;
+    A.poff[q] = pairs_of(c->L, c->bottom_from, l0 + q);
+    const int plane = s.nx / 2 * s.ny;
+    A.xoff[q] = off + plane;  // a plane of zeros below and above
+    off += (s.nz + 2) * plane;
+  }
+  A.x0 = wsp<T>(c, c->L.lv[l0].x);
+  A.b0 = wsp<T>(c, c->L.lv[l0].b);
+  if (l1 < (int)c->L.shapes.size() - 1) {
+    A.ld = MAP_LD<T>;
+    A.Ainv = wsp<const T>(c, c->L.maps);
+    A.Afirst = A.Ainv + MAP_CELLS * A.ld;
+  } else {
+    A.ld = c->nc;
+    A.Ainv = A.Afirst = wsp<const T>(c, c->L.cinv);
+  }
+  A.nu_pre = c->opt.nu_pre;
+  A.nu_post = c->opt.nu_post;
+  return A;
+}
+
+// What the bottom kernel reads: the packed pairs and, with a 4 x 4 x 4 level,
+// its maps (its cycles on the unit vectors).
+template <typename T>
+void bottom_setup(gmg_ctx* c) {
+  const int nl = (int)c->L.shapes.size(), l0 = c->bottom_from;
+  PackArgs<T> P{};
+  P.nlev = nl - 1 - l0;
+  P.npairs = pairs_of(c->L, l0, nl - 1);
+  P.w = wsp<T>(c, c->L.pack);
+  for (int q = 0; q < P.nlev; ++q) {
+    P.co[q] = face_coef<T>(c, l0 + q);
+    P.g[q] = c->L.shapes[l0 + q].geom();
+    P.poff[q] = pairs_of(c->L, l0, l0 + q);
+  }
+  GMG_LAUNCH(c, "bottom_pack", k_bottom_pack<T>,
+             (Launch{dim3((unsigned)(P.npairs + 255) / 256), dim3(256, 1, 1), 0}), P);
+  if (!c->L.maps) return;
+  const Launch all{dim3(2 * MAP_CELLS), dim3(BottomShape<T>::threads, 1, 1), 0};
+  BottomArgs<T> A = bottom_args<T>(c, nl - 2, nl - 1);
+  A.b0 = nullptr;
+  A.x0 = wsp<T>(c, c->L.maps);
+  GMG_LAUNCH(c, "bottom_maps", (k_vcycle_bottom<T, true>), all, A);
+}
+
 // Hierarchy of the coefficient c->a, queued without a wait: its check (finite
 // and positive) and float32 copy in one pass, the faces of every level in both
 // precisions, the coarsest inverse; then one read-back decides.  (A refused
@@ -463,6 +543,12 @@ int build_hierarchy(gmg_ctx* c) {
     }
   }
   coarse_inverse(c);
+  if (c->bottom_from >= 0) {
+    if (c->mixed)
+      bottom_setup<float>(c);
+    else
+      bottom_setup<double>(c);
+  }
   if (read_back(c, misc + MISC_RENEWAL, 3) != GMG_OK) return GMG_ERR_HIP;
   if (c->pinned[1] > 0) return GMG_ERR_NONFINITE;
   if (!(c->pinned[0] > 0.0)) return GMG_ERR_ARG;
@@ -726,37 +812,13 @@ void coarse_solve(gmg_ctx* c, const T* b, T* x) {
              wsp<const T>(c, c->L.cinv), b, x, n);
 }
 
-// Arguments of the bottom kernel.
-template <typename T>
-BottomArgs<T> bottom_args(gmg_ctx* c) {
-  const int nl = (int)c->L.shapes.size(), l0 = c->bottom_from;
-  BottomArgs<T> A{};
-  A.nlev = nl - l0;
-  int off = 0;
-  for (int q = 0; q < A.nlev; ++q) {
-    const LevelShape& s = c->L.shapes[l0 + q];
-    A.co[q] = face_coef<T>(c, l0 + q);
-    A.g[q] = s.geom();
-    if (q == A.nlev - 1) break;
-    const int plane = s.nx / 2 * s.ny;
-    A.xoff[q] = off + plane;  // a plane of zeros below and above
-    off += (s.nz + 2) * plane;
-  }
-  A.x0 = wsp<T>(c, c->L.lv[l0].x);
-  A.b0 = wsp<T>(c, c->L.lv[l0].b);
-  A.Ainv = wsp<const T>(c, c->L.cinv);
-  A.nu_pre = c->opt.nu_pre;
-  A.nu_post = c->opt.nu_post;
-  return A;
-}
-
 // The levels from bottom_from down to the coarsest in one workgroup
 // (k_vcycle_bottom): a V-cycle, or the full multigrid cycle over those
 // levels when fmg.
 template <typename T>
 void vcycle_bottom(gmg_ctx* c, int fmg) {
   const Launch one{dim3(1), dim3(BottomShape<T>::threads, 1, 1), 0};
-  const BottomArgs<T> A = bottom_args<T>(c);
+  const BottomArgs<T> A = bottom_args<T>(c, c->bottom_from, (int)c->L.shapes.size() - (c->L.maps ? 2 : 1));
   if (fmg)
     GMG_LAUNCH(c, kname("fmg_bottom", c->bottom_from, sizeof(T)), (k_vcycle_bottom<T, true>), one, A);
   else

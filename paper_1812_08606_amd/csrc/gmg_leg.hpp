@@ -170,7 +170,7 @@ __global__ __launch_bounds__(LegShape<T>::threads) void k_leg(const LegArgs<T> A
           q[w].b[1] = A.b[A.hn + (c >> 1)];
         }
       } else {
-        pair_weights(q[w], A.co, g, m, j, k);
+        pair_weights(q[w], pair_faces(A.co, g, m, j, k), g, m, j, k);
         const T b0 = A.b[c], b1 = A.b[c + 1];
         q[w].b[0] = par ? b1 : b0;
         q[w].b[1] = par ? b0 : b1;
