@@ -668,8 +668,8 @@ void sym_face(gmg_ctx* c, int l, const T* Xin, T* Xout, const T* b, const FaceCo
   auto go = [&](auto wc) {
     constexpr int WX = decltype(wc)::value, R = FaceSymShape<T, WX>::R, iy = FaceSymShape<T, WX>::IY;
     const int gy = (s.ny + iy - 1) / iy;
-    // blocks of the kernel resident on one CU (one, for these 16- and 8-wave
-    // blocks and their registers), asked once
+    // blocks of the kernel resident on one CU (two of eight float32 waves, one
+    // of 16, one of eight float64 waves: registers), asked once
     static const int per_cu = [] {
       int nb = 0;
       return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sym_face<T, FIRST, WX>, 64 * WX * R, 0) ==

@@ -28,14 +28,16 @@ struct FaceCol {
   T hxo;           // old c2 value of the same column in the row beyond the block (rows 0 and R - 1)
 };
 
-// Block: 64 WX lanes per row (the whole row: no x-halo) times R = 16 / WX
-// rows (float32; 8 / WX in float64, whose registers would not fit 1024
-// threads), of which rows 0 and R - 1 are a halo (their c1 values feed rows 1
-// and R - 2 and are not stored).  Lane m owns pair m of row j = (R - 2) by
-// + r - 1 and marches a z-chunk: on iteration k it updates colour c1 on
-// plane k from the old iterate Xin (the other colour's old values of rows
-// j - 1 and j + 1 and of pairs m - 1 and m + 1 from an LDS stage of two
-// planes), writes the new value into an LDS ring of three planes, waits at
+// Block: 64 WX lanes per row (the whole row: no x-halo) times R rows: 16 / WX
+// in float32, 8 / WX in float64 (whose registers would not fit 1024 threads),
+// but 8 rows of one wave in both (in float32 two blocks then share a CU and
+// one's loads cover the other's barriers: 16.7 -> 15.3 us per sweep at 128^3,
+// though the halo is two rows of 8 instead of 16).  Of them rows 0 and R - 1
+// are a halo (their c1 values feed rows 1 and R - 2 and are not stored).  Lane
+// m owns pair m of row j = (R - 2) by + r - 1 and marches a z-chunk: on
+// iteration k it updates colour c1 on plane k from the old iterate Xin (the
+// other colour's old values of rows j - 1 and j + 1 and of pairs m - 1 and m +
+// 1 from an LDS stage of two planes), writes the new value into an LDS ring of three planes, waits at
 // a barrier, and updates colour c2 on plane k - 1 from the ring.  Planes
 // k0 - 1 and k1 get c1 only (for the c2 updates of the chunk's end planes).
 // FIRST: the first sweep from x = 0 (c1 = b / D; Xin not read).  Xout must
@@ -43,7 +45,7 @@ struct FaceCol {
 template <typename T, int WX>
 struct FaceSymShape {
   static constexpr int W = 64 * WX;
-  static constexpr int R = (sizeof(T) == 4 ? 16 : 8) / WX;
+  static constexpr int R = WX == 1 ? 8 : (sizeof(T) == 4 ? 16 : 8) / WX;
   static constexpr int IY = R - 2;
   static_assert(IY >= 1, "a block needs a row that owns cells");
 };
