@@ -639,21 +639,25 @@ constexpr int FACE_MAX_WAVES = sizeof(T) == 4 ? 4 : 2;
 // Seidel with both smoothing phases, rows of at most 256 pairs in float32
 // and 128 in float64 (a block spans the row: with two waves 8 rows in
 // float32 and 4 in float64, of which 6 and 2 own cells; float64 at 256^3:
-// 258 us per sweep against 2 x 163 us for the half-sweeps); on request, or
-// by default on levels of at least 128^3 cells.  They read the face coefficients once per
-// sweep instead of twice; on smaller levels, where a sweep is latency-bound,
-// the fused kernel takes as long as the two half-sweep kernels it replaces
-// (kernel trace of 256^3 solves: 12.2 us against 2 x 5.7 us at 64^3 and
-// below), and fewer launches did not shorten the solves (with z-chunks of
-// one or two planes there, 10.3 us per fused sweep, the 64^3 mixed step
-// took 3.71 ms against 3.49 and the 512^3 one 87.8 against 87.0).
+// 258 us per sweep against 2 x 163 us for the half-sweeps); on request, or by
+// default on levels of at least 128^3 cells, and from 2^19 cells where a row
+// fills more than half of one wave.  They read the face coefficients once per
+// sweep instead of twice.  (V-cycles, half-sweeps against fused on level 1:
+// 88 x 104 x 120 float32 338 against 329 us, float64 540 against 529; 104 x
+// 120 x 96 333 and 322, 548 and 533; but 32 pairs a row, 64 x 256 x 64,
+// float64 465 and 468, and rows of several waves, 192 x 80 x 64 float64 514
+// and 523, 512 x 48 x 48 float32 364 and 369.)  On smaller levels, where a
+// sweep is latency-bound, the fused kernel takes as long as the two half-sweep
+// kernels it replaces (kernel trace of 256^3 solves: 12.2 us against 2 x 5.7
+// us at 64^3 and below).
 template <typename T>
 bool fused_face(gmg_ctx* c, int l) {
   const LevelShape& s = c->L.shapes[l];
   const int fs = c->opt.fine_sweep;
   return c->opt.smoother == GMG_SMOOTH_RBGS && c->opt.nu_pre >= 1 && c->opt.nu_post >= 1 && l >= 1 &&
          l < (int)c->L.shapes.size() - 1 && face_waves(s) <= FACE_MAX_WAVES<T> &&
-         (fs == GMG_SWEEP_FUSED || (fs == GMG_SWEEP_AUTO && s.n() >= ((size_t)1 << 21)));
+         (fs == GMG_SWEEP_FUSED ||
+          (fs == GMG_SWEEP_AUTO && s.n() >= (size_t)1 << (face_waves(s) == 1 && s.nx > 64 ? 19 : 21)));
 }
 
 // One fused symmetric sweep on coarse level l: colour c1 from Xin into Xout,

@@ -31,3 +31,25 @@ def test_fused_rows_match_half_sweeps(shape):
             assert ("sym_L1_" + sfx in s.profile_read()) == (sweep == "fused")
         for z, r in zip(out["fused"], out["half"]):
             assert ((z - r).norm() / r.norm()).item() < tol
+
+
+# level 1 by default fused from 2^19 cells where a row fills more than half of
+# one wave (legs run up to 2^20 cells in float32, 2^19 in float64)
+@pytest.mark.parametrize("shape,fused", [((176, 208, 240), (True, True)), ((128, 320, 256), (False, False)),
+                                         ((144, 192, 160), (False, True)), ((272, 160, 160), (False, False))])
+def test_default_level_one_sweeps(shape, fused):
+    """Which sweeps the default takes, and its V-cycle against half-sweeps
+    (tolerances as above)."""
+    nx, ny, nz = shape
+    print(f"default sweeps {shape}", flush=True)
+    rng = np.random.default_rng(nx + ny + nz)
+    a = torch.tensor(np.exp(rng.uniform(-0.5, 0.5, (nz, ny, nx)) * np.log(1e2)), device=DEV)
+    v = torch.tensor(rng.standard_normal((nz, ny, nx)), device=DEV)
+    for precision, tol, sfx, want in (("mixed", 1e-5, "f32", fused[0]), ("fp64", 1e-13, "f64", fused[1])):
+        out = {}
+        for sweep in ("half", "auto"):
+            s = gm.GMGPoisson(a, precision=precision, fine_sweep=sweep)
+            s.profile(True)
+            out[sweep] = s.vcycle(v)
+            assert ("sym_L1_" + sfx in s.profile_read()) == (sweep == "auto" and want)
+        assert ((out["auto"] - out["half"]).norm() / out["half"].norm()).item() < tol
