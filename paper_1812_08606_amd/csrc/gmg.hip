@@ -1671,8 +1671,8 @@ void init_residual(gmg_ctx* c, const double* f, const double* x, double pb, doub
 // with four blocks per CU and 1290-1430 with 16-byte loads; the second stage
 // then adds 512 partials instead of 16384, 11.3 -> 7.3 us).
 // Launches of the vector-count templates (NV = 1..MAXV) through tables.
-Launch red_flat(gmg_ctx* c) {
-  const size_t b = std::min<size_t>((c->N + NTHREADS - 1) / NTHREADS, 2 * (size_t)c->cus);
+Launch red_flat(gmg_ctx* c, int per_cu = 2) {
+  const size_t b = std::min<size_t>((c->N + NTHREADS - 1) / NTHREADS, (size_t)per_cu * c->cus);
   return Launch{dim3((unsigned)std::max<size_t>(b, 1)), dim3(BX, BY, 1), 0};
 }
 
@@ -2096,8 +2096,10 @@ void lincomb(gmg_ctx* c, double* y, const double* x0, double c0, const double* x
 }
 
 // (w, u_q) for nv (1 or 2) vectors u_q at stride ldv from U, into out (device).
+// Eight blocks per CU: with two, one vector's loads left the memory idle (512 x
+// 512 x 640: 667 us, with eight 400; two vectors 816 and 768, with sixteen 803).
 void kdots(gmg_ctx* c, const double* w, const double* U, int nv, double* out) {
-  const Launch fl = red_flat(c);
+  const Launch fl = red_flat(c, 8);
   if (nv == 1)
     launch_dot<1>(c, fl, w, U);
   else

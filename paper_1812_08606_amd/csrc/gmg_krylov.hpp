@@ -34,12 +34,28 @@ __global__ __launch_bounds__(NTHREADS) void k_lincomb3(double* y, const double* 
                                                        const double* x2, double c0, double c1, double c2, size_t n,
                                                        int want_norm, double* __restrict__ partials) {
   double acc[1] = {0.0};
-  GMG_FLAT_LOOP(c, n) {
-    double v = c0 * x0[c];
-    if (x1) v += c1 * x1[c];
-    if (x2) v += c2 * x2[c];
-    y[c] = v;
-    acc[0] += v * v;
+  // U elements of a thread loaded per wait (y may be an input, so the compiler
+  // keeps each store before the next load: 20.7 -> 13.9 us at 128 x 128 x 160)
+  constexpr int U = 4;
+  const size_t stride = (size_t)gridDim.x * NTHREADS;
+  for (size_t c = (size_t)blockIdx.x * NTHREADS + threadIdx.y * BX + threadIdx.x; c < n; c += U * stride) {
+    double v0[U], v1[U], v2[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const size_t cu = c + u * stride < n ? c + u * stride : c;
+      v0[u] = x0[cu];
+      v1[u] = x1 ? x1[cu] : 0.0;
+      v2[u] = x2 ? x2[cu] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (c + u * stride >= n) break;
+      double v = c0 * v0[u];
+      if (x1) v += c1 * v1[u];
+      if (x2) v += c2 * v2[u];
+      y[c + u * stride] = v;
+      acc[0] += v * v;
+    }
   }
   if (want_norm) block_store_partials<1>(acc, 1, partials, gridDim.x);
 }
