@@ -151,6 +151,11 @@ bool has_maps(const Layout& L) {
   return s.nx == 4 && s.ny == 4 && s.nz == 4;
 }
 
+// Bytes of the packed pairs of any bottom levels (at most BOTTOM_MAX_SUM / 2
+// pairs, seven chunks each in float64).
+constexpr size_t PACK_BYTES = BOTTOM_MAX_SUM / 2 * 16 * PackedPair<double>::chunks;
+static_assert(PACK_BYTES % 256 == 0 && PackedPair<float>::chunks <= PackedPair<double>::chunks, "alignment of the maps");
+
 // x-pairs of the levels l0 .. l1 - 1.
 int pairs_of(const Layout& L, int l0, int l1) {
   size_t n = 0;
@@ -231,12 +236,13 @@ int make_layout(int nx, int ny, int nz, double hx, double hy, double hz, const g
   L->scal = take((size_t)(L->m * (L->m + 2) + (L->m + 2) + 32) * 8);
   const size_t nc = last.n();
   L->cinv = take(nc * nc * L->tsize);
-  const int lb = cheb || o->restriction == GMG_RESTRICT_TRANSPOSE ? -1 : bottom_level(*L);
-  L->pack = lb < 0 ? 0 : take((size_t)pairs_of(*L, lb, nl - 1) * 16 *
-                              (mixed ? PackedPair<float>::chunks : PackedPair<double>::chunks));
-  L->maps = lb < 0 || !has_maps(*L)
-                ? 0
-                : take((size_t)2 * MAP_CELLS * L->tsize * (mixed ? MAP_LD<float> : MAP_LD<double>));
+  // the bottom kernel's packed pairs and maps, in the partials beyond the
+  // blocks of a reduction (the workspace stays as large as without them)
+  L->pack = L->partials + (size_t)MAXV * RED_BLOCKS * 8;
+  L->maps = has_maps(*L) ? L->pack + PACK_BYTES : 0;
+  static_assert(PACK_BYTES + (size_t)2 * MAP_CELLS * MAP_LD<double> * 8 <=
+                    (size_t)MAXV * (MAX_RED_BLOCKS - RED_BLOCKS) * 8,
+                "packed pairs and maps do not fit the partials' tail");
   // the Krylov basis is free during a renewal and holds the matrix unless the
   // grid has few levels
   L->cmat = !mixed ? 0 : nc * nc * 8 <= (size_t)nvslots * L->ldv * 8 ? L->V : take(nc * nc * 8);
@@ -254,7 +260,7 @@ struct Launch {
 
 // Column-marching launch over an nx x ny x nz grid with at most max_blocks
 // blocks (the reduction kernels keep one partial per block).
-Launch col_launch(int nx, int ny, int nz, int max_blocks = MAX_RED_BLOCKS) {
+Launch col_launch(int nx, int ny, int nz, int max_blocks = RED_BLOCKS) {
   const int gx = (nx + BX - 1) / BX;
   int gy = (ny + BY - 1) / BY;
   if ((long long)gx * gy > max_blocks) gy = std::max(1, max_blocks / gx);
@@ -1589,7 +1595,7 @@ void cycle_any(gmg_ctx* c, const double* u, const double* bscale, void* z, bool 
 // of BY threads, and z-chunks from the rounds model with four blocks per CU
 // resident (their occupancy): a marching column re-reads a plane at each end
 // of its chunk, and a last round with few blocks leaves CUs idle.  At most
-// MAX_RED_BLOCKS blocks (one partial per block and vector; rows strided
+// RED_BLOCKS blocks (one partial per block and vector; rows strided
 // beyond).  Measured against 16384 blocks: the operator with its dots 21.6 ->
 // 17.7 us at 128^3, 161 -> 147 at 256^3, 1231 -> 1230 at 512^3 (float32 z,
 // mean over five steps), the initial residual 16.6 -> 12.0, 84 -> 77 and 570
@@ -1598,9 +1604,9 @@ void cycle_any(gmg_ctx* c, const double* u, const double* bscale, void* z, bool 
 Launch march_launch(gmg_ctx* c, int lanes) {
   const int gx = (lanes + BX - 1) / BX;
   int gy = (c->ny + BY - 1) / BY;
-  if ((long long)gx * gy > MAX_RED_BLOCKS) gy = std::max(1, MAX_RED_BLOCKS / gx);
+  if ((long long)gx * gy > RED_BLOCKS) gy = std::max(1, RED_BLOCKS / gx);
   const long long cols = (long long)gx * gy;
-  const int max_gz = (int)std::max<long long>(1, MAX_RED_BLOCKS / cols);
+  const int max_gz = (int)std::max<long long>(1, RED_BLOCKS / cols);
   const int kc = rounds_kc(c->nz, cols, 4LL * c->cus, (c->nz + max_gz - 1) / max_gz, 2);
   return Launch{dim3(gx, gy, (c->nz + kc - 1) / kc), dim3(BX, BY, 1), kc};
 }
@@ -1678,7 +1684,7 @@ Launch red_flat(gmg_ctx* c, int per_cu = 2) {
 
 // Launch of the operator + multi-dot pass: lane pairs on colour-split z
 // (at least two levels), one cell per thread otherwise; at most
-// MAX_RED_BLOCKS blocks (one partial per block and vector).
+// RED_BLOCKS blocks (one partial per block and vector).
 Launch opdot_launch(gmg_ctx* c) {
   return c->L.shapes.size() == 1 ? red_launch(c) : march_launch(c, c->nx / 2);
 }
@@ -1977,13 +1983,13 @@ void cheb_step(gmg_ctx* c, int l, double* hcol, double* vs) {
     GMG_LAUNCH(c, kname("ssor", l, sizeof(T)), (k_gs_pair_face<T, false>), pl, E, (const T*)R, co, g, pl.kc, 1);
     GMG_LAUNCH(c, kname("ssor", l, sizeof(T)), (k_gs_pair_face<T, false>), pl, E, (const T*)R, co, g, pl.kc, 0);
     Launch rf = fl;
-    rf.grid.x = std::min<unsigned>(fl.grid.x, MAX_RED_BLOCKS);
+    rf.grid.x = std::min<unsigned>(fl.grid.x, RED_BLOCKS);
     GMG_LAUNCH(c, "cheb_convert_dots", (k_convert_dots<T, NV>), rf, (const T*)E, w, n, U, c->L.ldv, part);
     nb = rf.nblocks();
   }
   finalize(c, nb, NV, FIN_DOTS, hcol, vs, nullptr);
   Launch rf = flat_launch(n);
-  rf.grid.x = std::min<unsigned>(rf.grid.x, MAX_RED_BLOCKS);
+  rf.grid.x = std::min<unsigned>(rf.grid.x, RED_BLOCKS);
   GMG_LAUNCH(c, "axpy_norm", k_axpy_norm<NV>, rf, w, n, U, c->L.ldv, (const double*)hcol, (const double*)vs, 1,
              part);
   finalize(c, rf.nblocks(), 1, FIN_NORM, hcol + NV, nullptr, vs + NV);
@@ -2012,7 +2018,7 @@ int cheb_estimate(gmg_ctx* c) {
     const size_t n = c->L.shapes[l].n();
     const Launch fl = flat_launch(n);
     Launch rf = fl;
-    rf.grid.x = std::min<unsigned>(fl.grid.x, MAX_RED_BLOCKS);
+    rf.grid.x = std::min<unsigned>(fl.grid.x, RED_BLOCKS);
     double* V0 = kvec(c, 0);
     GMG_LAUNCH(c, "uniform_start", k_uniform_start, fl, V0, n, (unsigned long long)l);
     GMG_LAUNCH(c, "multidot", k_multidot<1>, rf, (const double*)V0, n, (const double*)V0, c->L.ldv,

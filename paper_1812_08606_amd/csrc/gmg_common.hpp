@@ -12,7 +12,11 @@ constexpr int BY = 4;
 constexpr int NTHREADS = BX * BY;
 constexpr int NWAVES = NTHREADS / 64;
 constexpr int MAXV = 16;              // vectors per multi-dot / multi-axpy launch
-constexpr int MAX_RED_BLOCKS = 16384;  // blocks of a reduction launch
+constexpr int MAX_RED_BLOCKS = 16384;  // x-tiles of the widest grid; the partials have room for as many blocks
+// Blocks of a reduction launch (more only on grids of more x-tiles than that,
+// which have no one-workgroup bottom levels): the tail of the partials holds
+// what the bottom kernel reads.
+constexpr int RED_BLOCKS = 13312;
 
 struct Geom {
   int nx, ny, nz;

@@ -36,3 +36,21 @@ def test_maps_and_packed_pairs(shape, nu):
                 z = fn(torch.tensor(f, device=DEV)).cpu().numpy()
                 r = ref(hier, f.astype(dtype)).astype(np.float64)
                 assert np.linalg.norm(z - r) <= tol * np.linalg.norm(r)
+
+
+@pytest.mark.parametrize("shape,precision", [((112, 72, 40), "fp64"), ((120, 88, 40), "mixed")])
+def test_packed_pairs_need_no_more_workspace(shape, precision):
+    """Grids whose workspace comes within 256 KiB of the library's static array
+    (which refuses larger ones): packed pairs and maps lie in the partials'
+    tail, and the solve on the array equals the solve on a workspace."""
+    nx, ny, nz = shape
+    print(f"static limit {shape} {precision}", flush=True)
+    rng = np.random.default_rng(nx)
+    a = torch.tensor(np.exp(rng.uniform(-0.5, 0.5, (nz, ny, nx)) * np.log(1e2)), device=DEV)
+    f = torch.tensor(rng.standard_normal((nz, ny, nx)), device=DEV)
+    s = gm.GMGPoisson(a, precision=precision)
+    limit = 64 << 20
+    assert limit - (256 << 10) - 4096 < s.workspace_bytes <= limit
+    out = torch.empty_like(f)
+    r = gm.fgmres_solve_static(a, f, 0.2, 0.7, 1e-8, out=out, precision=precision)
+    assert torch.equal(r.phi, s.solve(f, 0.2, 0.7, tol=1e-8).phi)
