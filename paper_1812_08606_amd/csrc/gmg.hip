@@ -1592,8 +1592,8 @@ void cycle_any(gmg_ctx* c, const double* u, const double* bscale, void* z, bool 
 // ---------------------------------------------------------------------------
 
 // Column-marching launch with `lanes` lanes per row (cells or x-pairs), rows
-// of BY threads, and z-chunks from the rounds model with four blocks per CU
-// resident (their occupancy): a marching column re-reads a plane at each end
+// of BY threads, and z-chunks from the rounds model with per_cu blocks per CU
+// resident (their occupancy, four up to 128 registers): a marching column re-reads a plane at each end
 // of its chunk, and a last round with few blocks leaves CUs idle.  At most
 // RED_BLOCKS blocks (one partial per block and vector; rows strided
 // beyond).  Measured against 16384 blocks: the operator with its dots 21.6 ->
@@ -1601,13 +1601,13 @@ void cycle_any(gmg_ctx* c, const double* u, const double* bscale, void* z, bool 
 // mean over five steps), the initial residual 16.6 -> 12.0, 84 -> 77 and 570
 // -> 555 us, dL/da 120 -> 100 us at 256^3.  (512, 768, 1280 and 1536 blocks
 // were 10 to 30% slower than 1024 somewhere.)
-Launch march_launch(gmg_ctx* c, int lanes) {
+Launch march_launch(gmg_ctx* c, int lanes, int per_cu = 4) {
   const int gx = (lanes + BX - 1) / BX;
   int gy = (c->ny + BY - 1) / BY;
   if ((long long)gx * gy > RED_BLOCKS) gy = std::max(1, RED_BLOCKS / gx);
   const long long cols = (long long)gx * gy;
   const int max_gz = (int)std::max<long long>(1, RED_BLOCKS / cols);
-  const int kc = rounds_kc(c->nz, cols, 4LL * c->cus, (c->nz + max_gz - 1) / max_gz, 2);
+  const int kc = rounds_kc(c->nz, cols, (long long)per_cu * c->cus, (c->nz + max_gz - 1) / max_gz, 2);
   return Launch{dim3(gx, gy, (c->nz + kc - 1) / kc), dim3(BX, BY, 1), kc};
 }
 Launch red_launch(gmg_ctx* c) { return march_launch(c, c->nx); }
@@ -1676,19 +1676,26 @@ void init_residual(gmg_ctx* c, const double* f, const double* x, double pb, doub
 // orthogonalisation at 512^3, mean over seven steps: 1276 us, against 1327
 // with four blocks per CU and 1290-1430 with 16-byte loads; the second stage
 // then adds 512 partials instead of 16384, 11.3 -> 7.3 us).
-// Launches of the vector-count templates (NV = 1..MAXV) through tables.
 Launch red_flat(gmg_ctx* c, int per_cu = 2) {
   const size_t b = std::min<size_t>((c->N + NTHREADS - 1) / NTHREADS, (size_t)per_cu * c->cus);
   return Launch{dim3((unsigned)std::max<size_t>(b, 1)), dim3(BX, BY, 1), 0};
 }
 
+// Dots of nv vectors.  Eight blocks per CU for one or two: with two, one
+// vector's loads left the memory idle (512 x 512 x 640: 667 us, with eight 400;
+// two vectors 816 and 768, with sixteen 803).
+Launch dots_flat(gmg_ctx* c, int nv) { return red_flat(c, nv <= 2 ? 8 : 2); }
+
 // Launch of the operator + multi-dot pass: lane pairs on colour-split z
 // (at least two levels), one cell per thread otherwise; at most
-// RED_BLOCKS blocks (one partial per block and vector).
-Launch opdot_launch(gmg_ctx* c) {
-  return c->L.shapes.size() == 1 ? red_launch(c) : march_launch(c, c->nx / 2);
+// RED_BLOCKS blocks (one partial per block and vector).  From eleven vectors on
+// the kernel has 130 to 141 registers and three blocks on a CU (sixteen vectors
+// at 320^3, float64: 1247 us, planned for four 1705).
+Launch opdot_launch(gmg_ctx* c, int nv) {
+  return c->L.shapes.size() == 1 ? red_launch(c) : march_launch(c, c->nx / 2, nv > 10 ? 3 : 4);
 }
 
+// Launches of the vector-count templates (NV = 1..MAXV) through tables.
 template <typename TZ, int NV>
 void launch_opdot(gmg_ctx* c, const Launch& rl, const TZ* z, double* w, const double* V) {
   const char* nm = sizeof(TZ) == 4 ? "op_multidot_zf32" : "op_multidot_zf64";
@@ -1758,10 +1765,10 @@ void arnoldi_step(gmg_ctx* c, int j) {
   double* hc = scal_hcol(c, j);
   cycle_any(c, V + (size_t)j * N, vs + j, Zb, c->fmg_now);
   ++c->nprec;
-  const Launch rl = opdot_launch(c);
-  const Launch fl = red_flat(c);
   double* w = V + (size_t)(j + 1) * N;
   const int nv = j + 1;
+  const Launch rl = opdot_launch(c, std::min(MAXV, nv));
+  const Launch fl = red_flat(c);
   const auto seq = std::make_index_sequence<MAXV>{};
   for (int q0 = 0; q0 < nv; q0 += MAXV) {
     const int nq = std::min(MAXV, nv - q0);
@@ -1772,8 +1779,9 @@ void arnoldi_step(gmg_ctx* c, int j) {
         opdot_nv<double>(nq, c, rl, (const double*)Zb, w, V, seq);
       finalize(c, rl.nblocks(), nq, FIN_DOTS, hc + q0, vs + q0, nullptr, q0);
     } else {
-      dot_nv(nq, c, fl, w, V + (size_t)q0 * N, seq);
-      finalize(c, fl.nblocks(), nq, FIN_DOTS, hc + q0, vs + q0, nullptr, q0);
+      const Launch dl = dots_flat(c, nq);
+      dot_nv(nq, c, dl, w, V + (size_t)q0 * N, seq);
+      finalize(c, dl.nblocks(), nq, FIN_DOTS, hc + q0, vs + q0, nullptr, q0);
     }
   }
   for (int q0 = 0; q0 < nv; q0 += MAXV) {
@@ -1959,7 +1967,7 @@ void cheb_step(gmg_ctx* c, int l, double* hcol, double* vs) {
       gs_split<T, false>(c, E, Bs, nullptr, nullptr, a, 1);
     }
     gs_split<T, false>(c, E, Bs, nullptr, nullptr, a, 0);
-    const Launch dl = opdot_launch(c);
+    const Launch dl = opdot_launch(c, NV);
     GMG_LAUNCH(c, "cheb_natural_dots", (k_split_to_natural_dots<T, NV>), dl, (const T*)E, c->L.hn, g, w, U,
                c->L.ldv, part, dl.kc);
     nb = dl.nblocks();
@@ -2102,10 +2110,8 @@ void lincomb(gmg_ctx* c, double* y, const double* x0, double c0, const double* x
 }
 
 // (w, u_q) for nv (1 or 2) vectors u_q at stride ldv from U, into out (device).
-// Eight blocks per CU: with two, one vector's loads left the memory idle (512 x
-// 512 x 640: 667 us, with eight 400; two vectors 816 and 768, with sixteen 803).
 void kdots(gmg_ctx* c, const double* w, const double* U, int nv, double* out) {
-  const Launch fl = red_flat(c, 8);
+  const Launch fl = dots_flat(c, nv);
   if (nv == 1)
     launch_dot<1>(c, fl, w, U);
   else
