@@ -165,7 +165,12 @@ int gmg_setup(int nx, int ny, int nz, double hx, double hy, double hz,
 
 /* Replace the coefficient (same grid) and rebuild the hierarchy: the
  * per-time-step renewal of operator and preconditioner (Sec. 2.1, last
- * paragraphs). */
+ * paragraphs).  The check of the coefficient runs with the rebuild, not before
+ * it: a refused coefficient (GMG_ERR_ARG, GMG_ERR_NONFINITE) leaves neither the
+ * old hierarchy nor a new one.  Until a renewal succeeds, the calls that read
+ * the coefficient or the hierarchy (fgmres_solve, gmg_krylov_solve,
+ * gmg_apply_operator, gmg_vcycle, gmg_fmg) return the refused renewal's status
+ * and write nothing; the others are not affected, and a_dev is not read again. */
 int gmg_update_coefficient(gmg_ctx* ctx, const double* a_dev);
 
 /* Change the stream later calls enqueue on. */

@@ -315,6 +315,7 @@ struct gmg_ctx {
   double hx, hy, hz;
   gmg_options opt;
   const double* a;
+  int renewed;  // status of the last renewal: while it is an error, a and the hierarchy are not to be read
   hipStream_t stream;
   char* ws;
   size_t ws_bytes;
@@ -517,8 +518,8 @@ void bottom_setup(gmg_ctx* c) {
 // Hierarchy of the coefficient c->a, queued without a wait: its check (finite
 // and positive) and float32 copy in one pass, the faces of every level in both
 // precisions, the coarsest inverse; then one read-back decides.  (A refused
-// coefficient leaves no usable hierarchy; the next renewal rebuilds all of
-// it.)  Waiting for the check before anything else, and a conversion launch per
+// coefficient leaves no usable hierarchy: the entry points that read it
+// return the refusal, usable_ctx, until a renewal has rebuilt all of it.)  Waiting for the check before anything else, and a conversion launch per
 // face array, took 168 us at 128^3 against 64, 1.35 ms at 512^3 against 0.90
 // (mixed).
 int build_hierarchy(gmg_ctx* c) {
@@ -1813,6 +1814,10 @@ void update_solution(gmg_ctx* c, double* phi, int k, bool set) {
 
 bool valid_ctx(gmg_ctx* c) { return c != nullptr; }
 
+// For the entry points that read the coefficient or the hierarchy: the status
+// with which the last renewal refused its coefficient, GMG_OK otherwise.
+int usable_ctx(gmg_ctx* c) { return c->renewed; }
+
 // ---------------------------------------------------------------------------
 // The other Krylov methods (Sec. 5.3, Table t1) on natural float64 vectors
 // held in the basis slots V[0..], scalars in misc[4..15].
@@ -2436,6 +2441,7 @@ int init_ctx(gmg_ctx* c, int nx, int ny, int nz, double hx, double hy, double hz
   c->hz = hz;
   c->opt = *opt;
   c->a = a_dev;
+  c->renewed = GMG_OK;  // (a context whose set-up fails is not handed out)
   c->stream = (hipStream_t)hip_stream;
   c->ws = (char*)ws;
   c->ws_bytes = ws_bytes;
@@ -2523,6 +2529,7 @@ int gmg_update_coefficient(gmg_ctx* c, const double* a_dev) {
   c->a = a_dev;
   int r = build_hierarchy(c);
   if (r == GMG_OK && cheb) r = c->mixed ? cheb_estimate<float>(c) : cheb_estimate<double>(c);
+  c->renewed = r;
   return r;
 }
 
@@ -2558,6 +2565,7 @@ int fgmres_core(gmg_ctx* c, const double* f_dev, double phi_bot, double phi_top,
   if (!valid_ctx(c) || !f_dev || !phi_dev) return GMG_ERR_ARG;
   if (!(tol >= 0.0) || !std::isfinite(phi_bot) || !std::isfinite(phi_top)) return GMG_ERR_ARG;
   if (res_hist_cap < 0 || (res_hist_cap > 0 && !res_hist)) return GMG_ERR_ARG;
+  if (const int refused = usable_ctx(c)) return refused;
   const int m = c->opt.restart;
   int it = 0, nhist = 0;
   auto push_hist = [&](double v) {
@@ -2769,6 +2777,7 @@ int gmg_krylov_solve(gmg_ctx* c, int method, const double* f_dev, double phi_bot
   const int slots = c->opt.restart + 1;
   if ((method == GMG_KRYLOV_CG || method == GMG_KRYLOV_FCG) && slots < 4) return GMG_ERR_ARG;
   if ((method == GMG_KRYLOV_CGS || method == GMG_KRYLOV_BICGSTAB) && slots < 8) return GMG_ERR_ARG;
+  if (const int refused = usable_ctx(c)) return refused;
   int st;
   int its = 0;
   double rel = NAN;
@@ -2804,6 +2813,7 @@ int gmg_krylov_solve(gmg_ctx* c, int method, const double* f_dev, double phi_bot
 
 int gmg_apply_operator(gmg_ctx* c, const double* x_dev, double* y_dev, double phi_bot, double phi_top) {
   if (!valid_ctx(c) || !x_dev || !y_dev) return GMG_ERR_ARG;
+  if (const int refused = usable_ctx(c)) return refused;
   auto a16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
   if (c->nx % 2 == 0 && a16(x_dev) && a16(c->a) && a16(y_dev)) {  // pairs are 16-byte loads and stores
     const Launch lp = march_launch(c, c->nx / 2);
@@ -2822,6 +2832,7 @@ namespace {
 // so a captured graph would rarely be replayed)
 int cycle_api(gmg_ctx* c, const double* v_dev, double* z_dev, bool fmg) {
   if (!valid_ctx(c) || !v_dev || !z_dev) return GMG_ERR_ARG;
+  if (const int refused = usable_ctx(c)) return refused;
   const bool split = c->L.shapes.size() > 1;
   if (c->mixed) {
     float* z32 = wsp<float>(c, c->L.Z);

@@ -210,6 +210,9 @@ class GMGPoisson:
 
     # -- operations -------------------------------------------------------
     def update_coefficient(self, a: torch.Tensor):
+        """Renewal for another coefficient on the same grid.  After a refused
+        one (GMGError), solve, krylov_solve, apply, vcycle and fmg raise the
+        same error until a renewal succeeds."""
         _check_field(a, self.shape, "a", self.device)
         st = self._call(self._lib.gmg_update_coefficient, _ptr(a))
         if st != OK:
