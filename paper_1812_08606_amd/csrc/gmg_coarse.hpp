@@ -97,13 +97,6 @@ __device__ __forceinline__ double readlane(double v, int lane) {
   return __builtin_bit_cast(double, int2{__builtin_amdgcn_readlane(w.x, lane), __builtin_amdgcn_readlane(w.y, lane)});
 }
 
-// 1 / d of a pivot: recip, a chain less than half as long as the division's
-// (every pivot waits for one); the division itself where recip is not finite.
-__device__ __forceinline__ double rcp_pivot(double d) {
-  const double y = recip(d);
-  return isfinite(y) ? y : 1.0 / d;
-}
-
 // Sweeps the whole NB x NB block in S (symmetric, positive definite; LDS,
 // [row][column]) and stores the result, -S^{-1}, in the diagonal tile bk of
 // A.  QB columns at a time: one wave sweeps their QB pivots on the 64 x QB
@@ -135,7 +128,7 @@ __device__ __forceinline__ void sweep_pivot_block(double* S, double* Wb, double*
         const int pr = QB * q + p;
         const double d = readlane(m[p], pr);
         fail |= !(d > 0.0) || !isfinite(d);
-        const double id = rcp_pivot(d);
+        const double id = recip(d);  // (every pivot waits for one: the division's chain is twice as long)
         const bool own = lane == pr;
         const double f = own ? 0.0 : m[p] * id;
 #pragma unroll

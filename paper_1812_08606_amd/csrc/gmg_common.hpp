@@ -24,16 +24,19 @@ struct Geom {
 };
 
 // 1 / d: the hardware reciprocal (1 ulp) in the float32 preconditioner; in
-// float64 the hardware's estimate (2^-24) and two Newton steps, which gave the
-// correctly rounded quotient for every one of 5e8 random d over 800 binades.
-// (A division also rescales its operands: with it the float64 sweeps were
-// slower, FGMRES at 256^3 19.22 -> 19.03 ms, BiCGSTAB at 128 x 128 x 160 2.99
-// -> 2.96.)
+// float64 the hardware's estimate (2^-24) and two Newton steps, then what the
+// steps turn into NaN: no finite y is changed by the two instructions after
+// them, which give infinity where the estimate overflowed (subnormal d below
+// 2^-1024), 0 for an infinite d and infinity for d = 0, as a division does.
+// (A division also rescales its operands: time step at 256 x 256 x 320 10.75
+// ms with it against 10.70, the 256^3 gradient step 18.93 against 18.83; without
+// the last two instructions the same as with them.)
 __device__ __forceinline__ float recip(float d) { return __builtin_amdgcn_rcpf(d); }
 __device__ __forceinline__ double recip(double d) {
   double y = __builtin_amdgcn_rcp(d);
   y = __builtin_fma(__builtin_fma(-d, y, 1.0), y, y);
-  return __builtin_fma(__builtin_fma(-d, y, 1.0), y, y);
+  y = __builtin_fma(__builtin_fma(-d, y, 1.0), y, y);
+  return __builtin_amdgcn_div_fixup(__builtin_fmin(y, __builtin_inf()), d, 1.0);
 }
 
 // Workgroups go to the chip's 8 XCDs (each with its own L2) round-robin in
