@@ -23,6 +23,7 @@
 #include "gmg_bottom.hpp"
 #include "gmg_coarse.hpp"
 #include "gmg_leg.hpp"
+#include "gmg_plan.hpp"
 #include "gmg_step.hpp"
 #include "gmg_krylov.hpp"
 #include "gmg_cheb.hpp"
@@ -333,6 +334,9 @@ struct gmg_ctx {
   };
   std::vector<std::array<std::vector<LegPlan>, 3>> legs;  // per level: pre from zero, pre from a guess, post
   int fine_form;    // FINE_*: kernels of the finest level's smoothing
+  // column-marching launches of the reductions and operator passes: one lane
+  // per cell, per x-pair, and per x-pair with three blocks on a CU
+  Launch march_cells, march_pairs, march_pairs3;
   bool fmg_now;     // the running solve preconditions with full multigrid cycles
   bool gmres_mode;  // GMRES: one preconditioned-vector slot, x updated by M (V y)
   int nprec;        // preconditioner applications of the running solve
@@ -600,39 +604,6 @@ Launch pair_launch(int nx, int ny, int nz, long long target, int min_kc, int tri
   int kc = (int)std::max<long long>(min_kc, (nz * cols + target - 1) / target);
   kc = small_grid_kc(nz, cols, std::min(kc, nz), trip);
   return Launch{dim3(gx, gy, (nz + kc - 1) / kc), dim3(BX, BY, 1), kc};
-}
-
-// z-chunk of a column-marching launch with `cols` blocks per chunk column
-// and `resident` blocks running at once: the chunk (at least min_kc planes, a
-// multiple of step) that minimises the rounds of blocks times the planes a
-// block marches (its chunk plus `extra`), the smallest chunk for each chunk
-// count, among chunks that give at least min_rounds rounds when any does; and
-// that product.  (A round with few blocks leaves most CUs idle: at level 1 of
-// the 512^3 grid, 11-plane chunks made 1032 blocks of one per CU, 4.03 rounds
-// on 256 CUs; 24-plane chunks, 473 blocks in 2 rounds, took 110.5 us per sweep
-// against 137.8.  An even chunk is chosen as such: rounding the best chunk
-// down instead made 2 rounds of 1, 285 us against 166 for the fused residual
-// sweep at 320^3.)
-struct Rounds {
-  int kc;
-  double planes;
-};
-inline Rounds rounds_of(int nz, long long cols, long long resident, int min_kc, int extra, int min_rounds = 1,
-                        int step = 1) {
-  const int first = std::max(step, (std::min(nz, min_kc) + step - 1) / step * step);
-  Rounds best{first, 1e300}, any{first, 1e300};
-  for (int kc = first; kc < nz + step; kc += step) {
-    const long long gz = (nz + kc - 1) / kc;
-    if (kc > first && (nz + kc - step - 1) / (kc - step) == gz) continue;  // a smaller chunk gives the same count
-    const long long rounds = (cols * gz + resident - 1) / resident;
-    const double cost = (double)rounds * (kc + extra);
-    if (cost < any.planes) any = {kc, cost};
-    if (rounds >= min_rounds && cost < best.planes) best = {kc, cost};
-  }
-  return best.planes < 1e300 ? best : any;
-}
-inline int rounds_kc(int nz, long long cols, long long resident, int min_kc, int extra, int min_rounds = 1) {
-  return std::min(nz, rounds_of(nz, cols, resident, min_kc, extra, min_rounds).kc);
 }
 
 // Waves per row of the coarse levels' fused sweep (a block spans the row),
@@ -1602,7 +1573,7 @@ void cycle_any(gmg_ctx* c, const double* u, const double* bscale, void* z, bool 
 // mean over five steps), the initial residual 16.6 -> 12.0, 84 -> 77 and 570
 // -> 555 us, dL/da 120 -> 100 us at 256^3.  (512, 768, 1280 and 1536 blocks
 // were 10 to 30% slower than 1024 somewhere.)
-Launch march_launch(gmg_ctx* c, int lanes, int per_cu = 4) {
+Launch march_launch(const gmg_ctx* c, int lanes, int per_cu) {
   const int gx = (lanes + BX - 1) / BX;
   int gy = (c->ny + BY - 1) / BY;
   if ((long long)gx * gy > RED_BLOCKS) gy = std::max(1, RED_BLOCKS / gx);
@@ -1611,9 +1582,13 @@ Launch march_launch(gmg_ctx* c, int lanes, int per_cu = 4) {
   const int kc = rounds_kc(c->nz, cols, (long long)per_cu * c->cus, (c->nz + max_gz - 1) / max_gz, 2);
   return Launch{dim3(gx, gy, (c->nz + kc - 1) / kc), dim3(BX, BY, 1), kc};
 }
-Launch red_launch(gmg_ctx* c) { return march_launch(c, c->nx); }
-// the same with one lane per x-pair of the finest level (nx even)
-Launch pair_red_launch(gmg_ctx* c) { return march_launch(c, c->nx / 2); }
+// (found once per context: every operator pass, residual and dL/da asks)
+void plan_marches(gmg_ctx* c) {
+  const int pairs = std::max(1, c->nx / 2);  // (used for even nx only)
+  c->march_cells = march_launch(c, c->nx, 4);
+  c->march_pairs = march_launch(c, pairs, 4);
+  c->march_pairs3 = march_launch(c, pairs, 3);
+}
 
 unsigned long long* host_flag(gmg_ctx* c) {
   return reinterpret_cast<unsigned long long*>(c->pinned + HOST_DOUBLES - 1);
@@ -1656,7 +1631,7 @@ void init_residual(gmg_ctx* c, const double* f, const double* x, double pb, doub
   // the pair kernel loads f and x (caller's buffers) as 16-byte vectors
   auto a16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
   const bool pairs = c->nx % 2 == 0 && a16(f) && a16(x) && a16(c->a);
-  const Launch rl = pairs ? pair_red_launch(c) : red_launch(c);
+  const Launch rl = pairs ? c->march_pairs : c->march_cells;
   double* misc = scal_misc(c);
   double* r = store ? wsp<double>(c, c->L.V) : (double*)nullptr;
   const Geom g = c->L.shapes[0].geom();
@@ -1693,7 +1668,7 @@ Launch dots_flat(gmg_ctx* c, int nv) { return red_flat(c, nv <= 2 ? 8 : 2); }
 // the kernel has 130 to 141 registers and three blocks on a CU (sixteen vectors
 // at 320^3, float64: 1247 us, planned for four 1705).
 Launch opdot_launch(gmg_ctx* c, int nv) {
-  return c->L.shapes.size() == 1 ? red_launch(c) : march_launch(c, c->nx / 2, nv > 10 ? 3 : 4);
+  return c->L.shapes.size() == 1 ? c->march_cells : nv > 10 ? c->march_pairs3 : c->march_pairs;
 }
 
 // Launches of the vector-count templates (NV = 1..MAXV) through tables.
@@ -1953,11 +1928,11 @@ void cheb_step(gmg_ctx* c, int l, double* hcol, double* vs) {
   int nb;
   if (l == 0) {
     if (((uintptr_t)c->a & 15) == 0) {  // a loaded as 16-byte vectors
-      const Launch rl = pair_red_launch(c);
+      const Launch rl = c->march_pairs;
       GMG_LAUNCH(c, "cheb_op_fine", k_op_pair<0>, rl, v, (const double*)(vs + j), c->a, g, r,
                  (const double*)nullptr, c->L.ldv, part, rl.kc);
     } else {
-      const Launch rl = red_launch(c);
+      const Launch rl = c->march_cells;
       GMG_LAUNCH(c, "cheb_op_fine", k_op_natural<0>, rl, v, (const double*)(vs + j), c->a, g, r,
                  (const double*)nullptr, c->L.ldv, part, rl.kc);
     }
@@ -2127,7 +2102,7 @@ void kdots(gmg_ctx* c, const double* w, const double* U, int nv, double* out) {
 // w = A x (homogeneous plates) with the dots (w, u_q), q < nv (1 or 2), into out.
 void kapply(gmg_ctx* c, const double* x, double* w, const double* U, int nv, double* out) {
   const bool pairs = c->nx % 2 == 0 && ((uintptr_t)c->a & 15) == 0;  // a loaded as 16-byte vectors
-  const Launch rl = pairs ? pair_red_launch(c) : red_launch(c);
+  const Launch rl = pairs ? c->march_pairs : c->march_cells;
   const Geom g = c->L.shapes[0].geom();
   double* part = wsp<double>(c, c->L.partials);
   const double* one = nullptr;
@@ -2470,6 +2445,7 @@ int init_ctx(gmg_ctx* c, int nx, int ny, int nz, double hx, double hy, double hz
   else
     plan_legs<double>(c);
   c->fine_form = c->mixed ? choose_fine_form<float>(c) : choose_fine_form<double>(c);
+  plan_marches(c);
   const int m = opt->restart;
   c->R.assign((size_t)m * m, 0.0);
   c->cs.assign(m, 0.0);
@@ -2816,7 +2792,7 @@ int gmg_apply_operator(gmg_ctx* c, const double* x_dev, double* y_dev, double ph
   if (const int refused = usable_ctx(c)) return refused;
   auto a16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
   if (c->nx % 2 == 0 && a16(x_dev) && a16(c->a) && a16(y_dev)) {  // pairs are 16-byte loads and stores
-    const Launch lp = march_launch(c, c->nx / 2);
+    const Launch lp = c->march_pairs;
     GMG_LAUNCH(c, "apply_bc", k_apply_bc_pair, lp, x_dev, c->a, c->L.shapes[0].geom(), phi_bot, phi_top, y_dev, lp.kc);
     note(c, hipStreamSynchronize(c->stream));
     return c->err == hipSuccess ? GMG_OK : GMG_ERR_HIP;
@@ -2872,7 +2848,7 @@ int gmg_face_flux_grad(gmg_ctx* c, const double* phi_dev, const double* lam_dev,
   if (!valid_ctx(c) || !phi_dev || !lam_dev || !dLda_dev) return GMG_ERR_ARG;
   auto a16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
   if (c->nx % 2 == 0 && a16(phi_dev) && a16(lam_dev) && a16(dLda_dev)) {
-    const Launch lc = march_launch(c, c->nx / 2);
+    const Launch lc = c->march_pairs;
     GMG_LAUNCH(c, "face_grad", k_face_grad_pair, lc, phi_dev, lam_dev, c->L.shapes[0].geom(), phi_bot, phi_top,
                dLda_dev, lc.kc);
   } else {
