@@ -328,10 +328,6 @@ struct gmg_ctx {
   int bottom_from;  // first level run by the one-workgroup bottom kernel (-1: none)
   // levels whose visits run as legs (k_leg): launches of the pre- and
   // post-smoothing, empty where the level runs per-sweep kernels
-  struct LegPlan {
-    int sweeps;  // symmetric sweeps of the launch
-    int tx, ty, tz, hx, hy;
-  };
   std::vector<std::array<std::vector<LegPlan>, 3>> legs;  // per level: pre from zero, pre from a guess, post
   int fine_form;    // FINE_*: kernels of the finest level's smoothing
   // column-marching launches of the reductions and operator passes: one lane
@@ -858,61 +854,6 @@ void cheb_smooth_face(gmg_ctx* c, int l, T* x, const T* b, const FaceCoef<T>& co
 // 323.  (All levels below included: 64^3 222 -> 170 us, 32^3 123 -> 104.)
 constexpr size_t LEG_MAX_BYTES = (size_t)4 << 20;
 
-// Time of one launch of a leg (clocks, a model fitted to the bottom kernel's
-// and the leg's measured phases): launch and first loads, then per pair of
-// the box with its halo the loads and each half-sweep, times the rounds of
-// blocks (one per CU).
-template <typename T>
-double leg_cost(long long blocks, int pairs, int nh, int cus) {
-  const double load = sizeof(T) == 4 ? 1.6 : 3.2, half = sizeof(T) == 4 ? 0.55 : 0.75;
-  return 9000.0 + (double)((blocks + cus - 1) / cus) * (4000.0 + pairs * (load + half * nh));
-}
-
-// The cheapest box for `sweeps` symmetric sweeps on level s: halo of 2 sweeps
-// cells (one more with the residual, one less from x = 0).
-template <typename T>
-bool leg_box(const LevelShape& s, int sweeps, bool zero, bool resid, int cus, gmg_ctx::LegPlan& best, double& cost) {
-  const int nh = 2 * sweeps, R = nh + (resid ? 1 : 0) - (zero ? 1 : 0), H = s.nx / 2;
-  cost = 1e300;
-  for (int tx = H;; tx = (tx + 1) / 2) {
-    const int hx = tx == H ? 0 : (R + 1) / 2;
-    for (int ty = 2; ty <= 16; ty += 2)
-      for (int tz = 2; tz <= 16; tz += 2) {
-        const int rx = tx + 2 * hx, ry = ty + 2 * R, rz = tz + 2 * R, pairs = rx * ry * rz;
-        if (pairs > LegShape<T>::max_pairs || rx * (ry + 2) * (rz + 2) + 2 > LegShape<T>::lds ||
-            tx * ty * tz > LegShape<T>::own)
-          continue;
-        const long long blocks = (long long)((H + tx - 1) / tx) * ((s.ny + ty - 1) / ty) * ((s.nz + tz - 1) / tz);
-        const double c = leg_cost<T>(blocks, pairs, nh, cus);
-        if (c < cost) {
-          cost = c;
-          best = {sweeps, tx, ty, tz, hx, R};
-        }
-      }
-    if (tx <= 8) break;
-  }
-  return cost < 1e300;
-}
-
-// Launches of one leg of nu sweeps: the split into launches that costs least.
-template <typename T>
-double leg_split(const LevelShape& s, int nu, bool zero, bool resid, int cus, std::vector<gmg_ctx::LegPlan>& out) {
-  double best = 1e300;
-  for (int first = 1; first <= std::min(nu, 3); ++first) {
-    gmg_ctx::LegPlan p{};
-    double c;
-    if (!leg_box<T>(s, first, zero, resid && first == nu, cus, p, c)) continue;
-    std::vector<gmg_ctx::LegPlan> rest;
-    if (first < nu) c += leg_split<T>(s, nu - first, false, resid, cus, rest);
-    if (c < best) {
-      best = c;
-      out.assign(1, p);
-      out.insert(out.end(), rest.begin(), rest.end());
-    }
-  }
-  return best;
-}
-
 template <typename T>
 void plan_legs(gmg_ctx* c) {
   const int nl = (int)c->L.shapes.size(), npre = c->opt.nu_pre, npost = c->opt.nu_post;
@@ -924,9 +865,10 @@ void plan_legs(gmg_ctx* c) {
     const LevelShape& s = c->L.shapes[l];
     if (s.n() * sizeof(T) > LEG_MAX_BYTES) continue;
     auto& p = c->legs[l];
-    const double a = leg_split<T>(s, npre, true, true, c->cus, p[0]);
-    const double b = leg_split<T>(s, npre, false, true, c->cus, p[1]);
-    const double d = leg_split<T>(s, npost, false, false, c->cus, p[2]);
+    LegSearch<T> search(s.nx, s.ny, s.nz, c->cus);
+    const double a = search.split(npre, true, true, p[0]);
+    const double b = search.split(npre, false, true, p[1]);
+    const double d = search.split(npost, false, false, p[2]);
     if (a >= 1e300 || b >= 1e300 || d >= 1e300) p = {};
   }
 }
@@ -934,7 +876,7 @@ void plan_legs(gmg_ctx* c) {
 bool has_legs(gmg_ctx* c, int l) { return !c->legs[l][2].empty(); }
 
 template <typename T, bool FINE>
-void launch_leg(gmg_ctx* c, int l, const gmg_ctx::LegPlan& p, LegArgs<T>& A, const char* name) {
+void launch_leg(gmg_ctx* c, int l, const LegPlan& p, LegArgs<T>& A, const char* name) {
   const LevelShape& s = c->L.shapes[l];
   A.g = s.geom();
   A.nh = 2 * p.sweeps;

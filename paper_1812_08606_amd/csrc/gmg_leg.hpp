@@ -3,6 +3,7 @@
 #pragma once
 
 #include "gmg_bottom.hpp"
+#include "gmg_plan.hpp"
 
 namespace gmg {
 
@@ -49,17 +50,6 @@ struct LegArgs {
   int start, c1, nh;
   int tx, ty, tz;       // owned box: pairs, rows, planes
   int hx, hy;           // halo: pairs; rows and planes
-};
-
-// Pairs of the box and its halo: at most PPT per thread, as many as the
-// registers hold (15 weights and right sides a pair).  LDS elements of one
-// colour: the pairs, a frame of one row and plane, and one before and after.
-template <typename T>
-struct LegShape {
-  static constexpr int threads = sizeof(T) == 4 ? 1024 : 512;
-  static constexpr int max_pairs = sizeof(T) == 4 ? 4096 : 2560;
-  static constexpr int lds = sizeof(T) == 4 ? 7168 : 4608;
-  static constexpr int own = 2048;
 };
 
 // Weights and diagonals of the pair (m, j, k) of the finest level (cell

@@ -3,6 +3,8 @@
 #pragma once
 
 #include <algorithm>
+#include <array>
+#include <vector>
 
 namespace gmg {
 
@@ -45,5 +47,101 @@ inline Rounds rounds_of(int nz, long long cols, long long resident, int min_kc, 
 inline int rounds_kc(int nz, long long cols, long long resident, int min_kc, int extra, int min_rounds = 1) {
   return std::min(nz, rounds_of(nz, cols, resident, min_kc, extra, min_rounds).kc);
 }
+
+// Pairs of the box and its halo: at most PPT per thread, as many as the
+// registers hold (15 weights and right sides a pair).  LDS elements of one
+// colour: the pairs, a frame of one row and plane, and one before and after.
+template <typename T>
+struct LegShape {
+  static constexpr int threads = sizeof(T) == 4 ? 1024 : 512;
+  static constexpr int max_pairs = sizeof(T) == 4 ? 4096 : 2560;
+  static constexpr int lds = sizeof(T) == 4 ? 7168 : 4608;
+  static constexpr int own = 2048;
+};
+
+// One launch of a leg.
+struct LegPlan {
+  int sweeps;          // symmetric sweeps
+  int tx, ty, tz;      // owned box: pairs, rows, planes
+  int hx, hy;          // halo: pairs; rows and planes
+};
+
+// Time of one launch of a leg (clocks, a model fitted to the bottom kernel's
+// and the leg's measured phases): launch and first loads, then per pair of
+// the box with its halo the loads and each half-sweep, times the rounds of
+// blocks (one per CU).
+template <typename T>
+double leg_cost(long long blocks, int pairs, int nh, int cus) {
+  const double load = sizeof(T) == 4 ? 1.6 : 3.2, half = sizeof(T) == 4 ? 0.55 : 0.75;
+  return 9000.0 + (double)((blocks + cus - 1) / cus) * (4000.0 + pairs * (load + half * nh));
+}
+
+// Launches of the legs of one level: the boxes and the splits that cost least.
+template <typename T>
+class LegSearch {
+ public:
+  LegSearch(int nx, int ny, int nz, int cus) : nx_(nx), ny_(ny), nz_(nz), cus_(cus) {}
+
+  // A leg of nu sweeps (from x = 0 when zero, the residual after it when
+  // resid) as launches of one to three sweeps; their cost, 1e300 when there is
+  // none.  The cheapest way to run the last n sweeps, which start from an
+  // iterate, is found for n = 1, 2, ...  (a leg splits in 81 ways at 8 sweeps:
+  // trying each took 0.6 ms of the set-up per level, this 0.02).
+  double split(int nu, bool zero, bool resid, std::vector<LegPlan>& out) {
+    std::vector<double> cost(nu + 1, 1e300);
+    std::vector<int> first(nu + 1, 0);
+    cost[0] = 0.0;
+    for (int n = 1; n <= nu; ++n)
+      for (int f = 1; f <= std::min(n, 3); ++f) {
+        const Box& b = box(f, zero && n == nu, resid && f == n);
+        if (b.cost < 1e300 && b.cost + cost[n - f] < cost[n]) {
+          cost[n] = b.cost + cost[n - f];
+          first[n] = f;
+        }
+      }
+    out.clear();
+    if (cost[nu] < 1e300)
+      for (int n = nu; n > 0; n -= first[n]) out.push_back(box(first[n], zero && n == nu, resid && first[n] == n).plan);
+    return cost[nu];
+  }
+
+ private:
+  struct Box {
+    bool known = false;
+    double cost = 1e300;
+    LegPlan plan{};
+  };
+
+  // The cheapest box for `sweeps` symmetric sweeps: halo of 2 sweeps cells (one
+  // more with the residual, one less from x = 0).
+  const Box& box(int sweeps, bool zero, bool resid) {
+    Box& best = boxes_[(sweeps - 1) * 4 + zero * 2 + resid];
+    if (best.known) return best;
+    best.known = true;
+    const int nh = 2 * sweeps, R = nh + (resid ? 1 : 0) - (zero ? 1 : 0), H = nx_ / 2;
+    for (int tx = H;; tx = (tx + 1) / 2) {
+      const int hx = tx == H ? 0 : (R + 1) / 2;
+      for (int ty = 2; ty <= 16; ty += 2)
+        for (int tz = 2; tz <= 16; tz += 2) {
+          const long long rx = tx + 2 * hx, ry = ty + 2 * R, rz = tz + 2 * R;
+          if (rx * ry * rz > LegShape<T>::max_pairs || rx * (ry + 2) * (rz + 2) + 2 > LegShape<T>::lds ||
+              tx * ty * tz > LegShape<T>::own)
+            continue;
+          const long long blocks =
+              (long long)((H + tx - 1) / tx) * ((ny_ + ty - 1) / ty) * ((nz_ + tz - 1) / tz);
+          const double c = leg_cost<T>(blocks, (int)(rx * ry * rz), nh, cus_);
+          if (c < best.cost) {
+            best.cost = c;
+            best.plan = {sweeps, tx, ty, tz, hx, R};
+          }
+        }
+      if (tx <= 8) break;
+    }
+    return best;
+  }
+
+  int nx_, ny_, nz_, cus_;
+  std::array<Box, 12> boxes_;
+};
 
 }  // namespace gmg
