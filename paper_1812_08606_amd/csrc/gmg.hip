@@ -2308,8 +2308,9 @@ namespace {
 // each, at most HOST_BUFFERS_KEPT; the rest go back to the system):
 // allocating and freeing one took most of the 75 us that creating and
 // destroying a context adds to its renewal.  Portable across devices.  Every
-// entry point has waited for its launches when it returns, so nothing writes
-// to a buffer that is given back.
+// launch that writes to a buffer is waited for before its entry point returns
+// (the flag, its last write there, or the stream), so nothing writes to a
+// buffer that is given back.
 constexpr size_t HOST_BUFFERS_KEPT = 16;
 std::atomic<unsigned long long> g_contexts{0};
 std::mutex g_host_mu;
@@ -2501,7 +2502,11 @@ int fgmres_core(gmg_ctx* c, const double* f_dev, double phi_bot, double phi_top,
     phi_zero = false;
   };
   auto finish = [&](int status, double relres) {
-    zero_phi();
+    if (phi_zero) {  // (nothing after the fill waits for it)
+      zero_phi();
+      note(c, hipStreamSynchronize(c->stream));
+      if (c->err != hipSuccess) status = GMG_ERR_HIP;
+    }
     if (iterations) *iterations = it;
     if (res_hist_len) *res_hist_len = std::min(nhist, res_hist_cap);
     if (final_true_relres) *final_true_relres = relres;
@@ -2529,10 +2534,8 @@ int fgmres_core(gmg_ctx* c, const double* f_dev, double phi_bot, double phi_top,
       bnorm = std::sqrt(bn2);
       if (bnorm == 0.0) {
         phi_zero = true;
-        zero_phi();
-        note(c, hipStreamSynchronize(c->stream));
         push_hist(0.0);
-        return finish(c->err == hipSuccess ? GMG_OK : GMG_ERR_HIP, 0.0);
+        return finish(GMG_OK, 0.0);
       }
       push_hist(beta / bnorm);
       first = false;
