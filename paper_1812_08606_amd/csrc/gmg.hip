@@ -15,6 +15,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -2311,19 +2312,23 @@ namespace {
 // launch that writes to a buffer is waited for before its entry point returns
 // (the flag, its last write there, or the stream), so nothing writes to a
 // buffer that is given back.
+// The pool is a plain array: a context may be destroyed from a static
+// destructor or an exit handler, after any destructor this library could have
+// for it has run, and giving a buffer back allocates nothing.
 constexpr size_t HOST_BUFFERS_KEPT = 16;
+struct HostPool {
+  std::mutex mu;
+  double* free[HOST_BUFFERS_KEPT];
+  size_t kept;
+};
+static_assert(std::is_trivially_destructible<HostPool>::value, "the pool must outlive every context");
+HostPool g_host{};
 std::atomic<unsigned long long> g_contexts{0};
-std::mutex g_host_mu;
-std::vector<double*> g_host_free;
 
 double* host_buffer_take() {
   {
-    std::lock_guard<std::mutex> g(g_host_mu);
-    if (!g_host_free.empty()) {
-      double* p = g_host_free.back();
-      g_host_free.pop_back();
-      return p;
-    }
+    std::lock_guard<std::mutex> g(g_host.mu);
+    if (g_host.kept) return g_host.free[--g_host.kept];
   }
   double* p = nullptr;
   if (hipHostMalloc((void**)&p, HOST_DOUBLES * 8, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
@@ -2335,10 +2340,9 @@ double* host_buffer_take() {
 
 void host_buffer_give(double* p) {
   {
-    std::lock_guard<std::mutex> g(g_host_mu);
-    if (g_host_free.size() < HOST_BUFFERS_KEPT) {
-      if (g_host_free.capacity() == 0) g_host_free.reserve(HOST_BUFFERS_KEPT);
-      g_host_free.push_back(p);
+    std::lock_guard<std::mutex> g(g_host.mu);
+    if (g_host.kept < HOST_BUFFERS_KEPT) {
+      g_host.free[g_host.kept++] = p;
       return;
     }
   }
