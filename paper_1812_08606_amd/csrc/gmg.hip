@@ -2331,7 +2331,9 @@ double* host_buffer_take() {
     if (g_host.kept) return g_host.free[--g_host.kept];
   }
   double* p = nullptr;
-  if (hipHostMalloc((void**)&p, HOST_DOUBLES * 8, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+  // coherent: the host sees the flag while the kernel that wrote it still runs
+  if (hipHostMalloc((void**)&p, HOST_DOUBLES * 8,
+                    hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
     (void)hipGetLastError();
     return nullptr;
   }
