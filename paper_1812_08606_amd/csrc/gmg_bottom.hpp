@@ -452,23 +452,33 @@ __global__ __launch_bounds__(BottomShape<T>::threads) void k_vcycle_bottom(const
         if (!(t & (per - 1))) x[r] = acc;
       }
     } else {
-      // eight rows of the inverse per wave at a time, the lanes across the row
-      const int lane = t & 63, wave = t >> 6;
-      for (int r0 = 8 * wave; r0 < nc; r0 += 8 * (NT / 64)) {
-        T acc[8];
+      // A row per lane, the rows rounded up to whole waves, and the columns
+      // dealt to the S groups of so many lanes that the workgroup holds (the
+      // inverse is symmetric: consecutive rows read consecutive elements of a
+      // column); U columns per wait.  One workgroup reads the whole inverse, so
+      // the bytes a CU can have in flight bound it.  (Eight rows per wave with
+      // the lanes across a row waited for eight loads at a time: V-cycle of 4158
+      // cells and below, 462 in the coarsest, float64 80.6 -> 51.8 us, float32
+      // 42.8 -> 32.5.)
+      constexpr int U = 16;
+      const int P = (nc + 63) & ~63, S = NT / P, h = (t >> 6) / (P >> 6), r = t - h * P;
+      if (h < S) {
+        const T* col = A.Ainv + min(r, nc - 1);
+        T acc[4] = {T(0), T(0), T(0), T(0)};
+        for (int c0 = h; c0 < nc; c0 += S * U) {
+          T a[U];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc[u] = T(0);
-        for (int c = lane; c < nc; c += 64) {
-          const T bv = lbc[c];
+          for (int u = 0; u < U; ++u) a[u] = col[(size_t)min(c0 + u * S, nc - 1) * ld];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) acc[u] += A.Ainv[(size_t)min(r0 + u, nc - 1) * ld + c] * bv;
+          for (int u = 0; u < U; ++u) acc[u & 3] += c0 + u * S < nc ? a[u] * lbc[c0 + u * S] : T(0);
         }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-#pragma unroll
-          for (int off = 32; off > 0; off >>= 1) acc[u] += __shfl_down(acc[u], off, 64);
-          if (lane == 0 && r0 + u < nc) x[r0 + u] = acc[u];
-        }
+        part[t] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+      }
+      lds_barrier();
+      if (t < nc) {
+        T acc = T(0);
+        for (int q = 0; q < S; ++q) acc += part[q * P + t];
+        x[t] = acc;
       }
     }
     lds_barrier();
