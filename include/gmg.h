@@ -121,14 +121,17 @@ typedef struct gmg_options {
                            the one-workgroup bottom with rows of at most 256
                            x-pairs in float32, 128 in float64; half-sweeps
                            elsewhere);
-                           GMG_SWEEP_AUTO (default): fused where it was
-                           measured faster (finest level: by row length and
-                           size, about 144^3 cells and up; coarse levels:
-                           at least 128^3 cells), and on levels
-                           whose iterate has at most 4 MiB several sweeps per
-                           kernel, with the interpolation or the residual
-                           restriction in it (nu_pre, nu_post >= 1, mean
-                           restriction) */
+                           GMG_SWEEP_AUTO (default): on levels whose iterate has
+                           at most 4 MiB (about 10^6 cells in float32, half of
+                           that in float64) several sweeps per kernel, with the
+                           interpolation or the residual restriction in it
+                           (nu_pre, nu_post >= 1, mean restriction); on larger
+                           finest levels half-sweeps, symmetric sweeps on tiles
+                           of 62 x-pairs or symmetric sweeps on whole rows (of
+                           at most 128 x-pairs), whichever a cost model of row
+                           length and size finds the shortest; on coarse levels
+                           one kernel per symmetric sweep from 2^21 cells, or
+                           from 2^19 where a row has 33 to 64 x-pairs */
   int cold_cycle;       /* preconditioner of a solve with use_x0 = 0: GMG_CYCLE_FMG
                            (default) one full multigrid cycle per step,
                            GMG_CYCLE_V one V-cycle per step. */
